@@ -207,7 +207,10 @@ SA_API int sa_quantize_bcq_terms(const float *w, int N, int K, int q, int group,
                                  int terms, int8_t *signs, int8_t *exps, int8_t *term_signs,
                                  void *stream);
 
-/* Launch geometry sa_shiftadd_gemm uses for a shape (host-only, no HIP call). */
+/* Launch geometry of the table kernels for a shape (host-only, no HIP call).
+ * sa_shiftadd_gemm and sa_shiftadd_gemm_f16 run them at batch 1, for groups that
+ * are not multiples of 128, for more than 4 planes and for small layers; other
+ * calls run matrix-core kernels with a geometry of their own. */
 typedef struct {
     int path;         /* 0: generic kernel (any group); group % 128 == 0: 1 row kernel
                          (batch 1), 2 batch kernel (batch >= 2); 3: the row kernel

@@ -1,0 +1,27 @@
+// Block-scaled matrix-core form of the layer for small batches (gemm_mx.hip):
+// what the entry points of shiftadd.hip need to choose and launch it.
+#ifndef SHIFTADD_GEMM_MX_H
+#define SHIFTADD_GEMM_MX_H
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace sa_mx {
+
+struct Args {
+    const uint16_t* x;      // activations [B][K]
+    const uint8_t* packed;  // planes, packed layout
+    const int8_t* exps;     // [q][N][K/G]
+    int q, N, K, G, B;
+    void* y;                // [B][N] fp32, or binary16 when out_half
+    int out_half;
+};
+
+// Whether this form takes a call with row-wise factors.
+bool takes(int q, int N, int K, int G, int B);
+
+void launch(const Args& a, hipStream_t s);
+
+}  // namespace sa_mx
+
+#endif

@@ -1,0 +1,479 @@
+// The layer for a few batch rows on the block-scaled matrix cores (gfx950).
+//
+//   y[b][n] = sum_i sum_g 2^e[i][n][g] * sum_{k in g} s_i[n][k] x[b][k]
+//
+// v_mfma_scale_f32_16x16x128_f8f6f4 multiplies fp4 by fp8 operands in blocks of
+// 32 columns, each block of each operand row with a power of two of its own.
+// That is this layer's form: the planes are +-1.0 in fp4, one VALU operation per
+// eight weights after a shift, and the factor 2^e of a (row, 128 columns) is
+// the operand's block scale, so nothing is shifted or added outside the matrix
+// core over the whole input dimension.
+//
+// Activations.  A binary16 activation is split into three fp8 (e4m3) pieces of
+// four significand bits each, x = S (p0 + p1 / 32 + p2 / 1024), S the power of
+// two that brings the largest of 32 columns below 16; the pieces are matrix
+// columns of their own, so they cost no extra instructions while
+// 4 * batch <= 16.  The split is exact for every x above 2^-13 of its block's
+// largest and off by at most 2^-24 of that largest otherwise.
+// The core adds products of eight consecutive columns in a window of 13 bits
+// below the largest (measured: 2^8 + 2^-5 is kept, 2^8 + 2^-6 is not, further
+// apart fp32); below 16 and down to e4m3's 2^-9 the pieces stay inside that
+// window, so these sums are exact and everything after them is fp32.
+// Measured against 64 bits (4096x4096 q=3, N(0,1) with outliers, 2-norm):
+// 6e-8 relative, against 1.2e-7 (batch 2-4) of the table kernel.
+//
+// What bounds it: at 28672x8192 q=3 the key stream (16.5 us as a plain read);
+// per 16 rows x 128 columns x plane a SIMD needs 25 ns (batch <= 4: 8 VALU
+// operations and one MFMA), the table kernel's queries about 100 ns.  Measured
+// against the table batch kernel (us, graph replay, weights rotated over 300
+// MB): 4096x4096 q=3 batch 2 8.1 -> 5.1, batch 4 8.2 -> 5.7, batch 8 9.2 -> 7.8;
+// 11008x4096 batch 4 12.5 -> 8.1; 28672x8192 batch 2 40.4 -> 22.0, batch 4
+// 40.8 -> 23.2, batch 8 73.4 -> 30.2; 8192x28672 batch 8 76.2 -> 41.8.
+#include "gemm_mx.h"
+
+#include "shiftadd.h"
+
+namespace sa_mx {
+namespace {
+
+typedef int int4_t __attribute__((ext_vector_type(4)));
+typedef int int8v_t __attribute__((ext_vector_type(8)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef short short2_t __attribute__((ext_vector_type(2)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kTile = 16;
+constexpr int kGroupBlocks = 4;   // 128-column blocks per group
+constexpr int kPieces = 3;        // fp8 pieces of an activation
+constexpr int kColBytes = 528;    // LDS bytes of one piece of one batch row over a group (512 + 16)
+// |x| from this binary16 pattern (63488) on would round to a first piece beyond the
+// binary16 range; it and what is not finite take plain_output
+constexpr uint32_t kSplitLimit = 0x7bc0u;
+constexpr int kMaxTiles = 8;      // row tiles of one wave
+
+__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
+
+struct KernelArgs {
+    Args a;
+    int tiles;             // 16-row tiles, spread over (workgroup, row set)
+    int shares;            // workgroups * row sets
+    int ksplit;            // waves that share the columns (power of two <= kWaves)
+    int sets;              // row sets of a workgroup: it has ksplit * sets waves
+    int NG;                // exponent groups of a row
+    uint32_t group_magic;  // block J is in group (J * magic) >> 32; 0: one block per group
+};
+
+__device__ inline void unrotate(const uint4 v, int r, uint32_t out[4]) {
+    const int s = (16 - r) & 15;
+    const uint32_t in[4] = {v.x, v.y, v.z, v.w};
+    uint32_t t[4], u[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        t[d] = __builtin_amdgcn_alignbyte(in[(d + 1) & 3], in[d], (uint32_t)(s & 3));
+#pragma unroll
+    for (int d = 0; d < 4; ++d) u[d] = (s & 4) ? t[(d + 1) & 3] : t[d];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) out[d] = (s & 8) ? u[(d + 2) & 3] : u[d];
+}
+
+// 32 signs as fp4 (e2m1) +-1.0: register v, nibble n holds bit 4n + v of the word.
+__device__ inline int8v_t expand(uint32_t w) {
+    int8v_t a = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        a[v] = (int)(((w << (3 - v)) & 0x88888888u) ^ 0xAAAAAAAAu);
+    return a;
+}
+
+// One output by plain summation, for calls the split does not represent
+// (activations that are not finite, a scale of 2^127).
+__device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
+    const int C = a.K >> 3, NG = a.K / a.G;
+    const int T = n >> 6, r = n & 63;
+    const int R = imin(64, a.N - 64 * T);
+    float y = 0.0f;
+#pragma unroll 1
+    for (int i = 0; i < a.q; ++i) {
+        const uint8_t* keys = a.packed + ((int64_t)i * a.N + 64 * T) * C + 16 * r;
+        const int8_t* e = a.exps + ((int64_t)i * a.N + n) * NG;
+        float s = 0.0f;
+        int c = 0;
+#pragma unroll 1
+        for (int g = 0; g < NG; ++g) {
+            s = 0.0f;
+#pragma unroll 1
+            for (; c < (g + 1) * (a.G >> 3); ++c) {
+                const uint32_t key = keys[(int64_t)(c >> 4) * 16 * R + ((c - r) & 15)];
+#pragma unroll 1
+                for (int j = 0; j < 8; ++j) {
+                    const float x = (float)__builtin_bit_cast(
+                        _Float16, a.x[(int64_t)b * a.K + 8 * c + j]);
+                    s += (key >> j) & 1 ? x : -x;
+                }
+            }
+            y += ldexpf(s, (int)e[g]);
+        }
+    }
+    return y;
+}
+
+// Work split.  Every workgroup owns whole rows: its waves are ksplit shares of
+// the input dimension (512-column groups ksl, ksl + ksplit, ...) times `sets`
+// sets of row tiles, so no partial sum leaves a workgroup.  One 8-wave
+// workgroup per CU: a second one would hide more latency but splits the
+// activations once more (28672x8192 batch 4: 23.2 us against 26.7 with 512
+// workgroups).  A wave splits the activations of its group into LDS that only
+// it reads (no barrier), keeps them as matrix operands in registers and runs
+// its row tiles through them, the next tile's keys requested before the
+// current tile's products.  The loops stay rolled: a workgroup runs them few
+// times and unrolled code would be fetched cold.
+//
+// Columns.  Lane (row r, block g) loads the 16 key bytes of one row and one of
+// the group's four blocks, rotates them to chunk order, and step m multiplies
+// 32 columns of each of the four blocks: register v, nibble n of the operand is
+// bit 4n + v of key word m.  The activations are stored in that order; the
+// second operand's lanes hold columns 16g..16g+15 and 64+16g.. of a step, which
+// is half a block's 32 columns each.
+template <int Q>
+struct Keys {
+    uint4 w[Q];
+    uint32_t e[Q];  // exponent byte of this lane's row and block
+};
+
+template <int Q, int CT, int NP>
+__device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
+    const Args& a = ka.a;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int ksl = wave & (ka.ksplit - 1);
+    const int C = a.K >> 3, C16 = C >> 4, NG = ka.NG;
+    const int groups = (C16 + kGroupBlocks - 1) / kGroupBlocks;
+
+    // activations of this lane: 16 columns of batch rows (lane >> 5), + 2, + 4, ...
+    const int xp = (lane >> 3) & 3, xm = (lane >> 1) & 3, xh = lane & 1;
+    auto load_x = [&](int jg, uint4 (&raw)[NP][2]) {
+        const int64_t off = 128 * (int64_t)imin(kGroupBlocks * jg + xp, C16 - 1) + 16 * (lane & 7);
+#pragma unroll
+        for (int t = 0; t < NP; ++t) {
+            const uint16_t* p = a.x + (int64_t)imin(2 * t + (lane >> 5), a.B - 1) * a.K + off;
+            raw[t][0] = *reinterpret_cast<const uint4*>(p);
+            raw[t][1] = *reinterpret_cast<const uint4*>(p + 8);
+        }
+    };
+    uint4 raw[NP][2];
+    if (ksl < groups) load_x(ksl, raw);
+    __builtin_amdgcn_sched_barrier(0);
+
+    const int r = lane & 15, g = lane >> 4;
+    const int sets = ka.sets, rset = wave / ka.ksplit;
+    // row tiles of this wave: the first `extra` shares take one more
+    const int share = (int)blockIdx.x * sets + rset;
+    const int base = ka.tiles / ka.shares, extra = ka.tiles - base * ka.shares;
+    const int ntiles = base + (share < extra ? 1 : 0);
+    const int tile0 = share * base + imin(share, extra);
+
+    // this wave's pieces [3 B][528 bytes], then its scales [B][4 blocks] words
+    constexpr int kMaxB = 4 * CT;
+    constexpr int kWaveBytes = kPieces * kMaxB * kColBytes + kMaxB * 16;
+    char* px = lds + wave * kWaveBytes;
+    char* ps = px + kPieces * kMaxB * kColBytes;
+
+    auto load_keys = [&](int jg, int t, Keys<Q>& k) {
+        const int n = imin(kTile * (tile0 + t) + r, a.N - 1);
+        const int J = imin(kGroupBlocks * jg + g, C16 - 1);
+        const int eg = ka.group_magic ? (int)__umulhi((uint32_t)J, ka.group_magic) : J;
+        const uint32_t eoff = (uint32_t)(n * NG + eg);
+        const int T = n >> 6, R = imin(64, a.N - 64 * T);
+        const uint32_t off = (uint32_t)(64 * T * C + 16 * (n & 63) + 16 * J * R);
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            k.e[i] = (reinterpret_cast<const uint8_t*>(a.exps) + (size_t)i * a.N * NG)[eoff];
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            k.w[i] = *reinterpret_cast<const uint4*>(a.packed + (size_t)i * a.N * C + off);
+    };
+    uint32_t bad = 0;  // an activation that is not finite, or a scale of 2^127
+    auto split_x = [&](int jg) {
+        const bool in = kGroupBlocks * jg + xp < C16;
+        const bool short_group = kGroupBlocks * (jg + 1) > C16;  // uniform
+#pragma unroll
+        for (int t = 0; t < NP; ++t) {
+            const int b = 2 * t + (lane >> 5);
+            uint32_t d[8] = {raw[t][0].x, raw[t][0].y, raw[t][0].z, raw[t][0].w,
+                             raw[t][1].x, raw[t][1].y, raw[t][1].z, raw[t][1].w};
+            if (short_group) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) d[u] = in ? d[u] : 0u;
+            }
+            half2_t hm = {(_Float16)0.0f, (_Float16)0.0f};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const half2_t h = __builtin_bit_cast(half2_t, d[u]);
+                hm = __builtin_elementwise_maximum(__builtin_elementwise_maximum(hm, h), -h);
+            }
+            uint32_t mx = __builtin_bit_cast(uint32_t, hm);
+            mx = max(mx & 0x7fffu, (mx >> 16) & 0x7fffu);
+            mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0xB1, 0xf, 0xf, true));
+            bad |= mx >= kSplitLimit;
+            const uint32_t E = max(mx >> 10, 1u);
+            const float S[3] = {__builtin_bit_cast(float, (E + 109u) << 23),
+                                __builtin_bit_cast(float, (E + 104u) << 23),
+                                __builtin_bit_cast(float, (E + 99u) << 23)};
+            uint32_t out[3][2][2];  // [piece][s][v & 1]
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    const uint32_t sel = o ? 0x07060302u : 0x05040100u;
+                    // columns v = 2s + o and v + 4 of the lane's two chunks
+                    const uint32_t c0 = __builtin_amdgcn_perm(d[2 + s], d[s], sel);
+                    const uint32_t c1 = __builtin_amdgcn_perm(d[6 + s], d[4 + s], sel);
+                    half2_t f0 = __builtin_bit_cast(half2_t, c0);
+                    half2_t f1 = __builtin_bit_cast(half2_t, c1);
+#pragma unroll
+                    for (int p = 0; p < kPieces; ++p) {
+                        short2_t w = {0, 0};
+                        w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(w, f0, S[p], false);
+                        w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(w, f1, S[p], true);
+                        const int wi = __builtin_bit_cast(int, w);
+                        out[p][s][o] = (uint32_t)wi;
+                        if (p + 1 < kPieces) {
+                            f0 -= __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wi, S[p], false);
+                            f1 -= __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wi, S[p], true);
+                        }
+                    }
+                }
+            if (b < a.B) {
+#pragma unroll
+                for (int p = 0; p < kPieces; ++p)
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        uint32_t* o = reinterpret_cast<uint32_t*>(
+                            px + (kPieces * b + p) * kColBytes + (xm * 8 + xp * 2 + s) * 16 +
+                            4 * xh);
+                        o[0] = out[p][s][0];
+                        o[2] = out[p][s][1];
+                    }
+                if (xh == 0)
+                    *reinterpret_cast<uint8_t*>(ps + (b * 4 + xp) * 4 + xm) = (uint8_t)(E + 108u);
+            }
+        }
+    };
+    auto wave_fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+
+    float tot[kMaxTiles][CT];
+#pragma unroll
+    for (int t = 0; t < kMaxTiles; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) tot[t][c] = 0.0f;
+
+    if (ksl < groups && ntiles > 0) {
+        Keys<Q> k;
+        load_keys(ksl, 0, k);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+        for (int jg = ksl; jg < groups; jg += ka.ksplit) {
+            const bool more = jg + ka.ksplit < groups;
+            split_x(jg);
+            wave_fence();
+            if (more) load_x(jg + ka.ksplit, raw);
+            // matrix column r is piece r & 3 of batch row r >> 2 (+ 4 per column
+            // tile); columns that stand for nothing repeat a neighbour's
+            int8v_t X[CT][4];
+            uint32_t xs[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int b = imin(4 * c + (r >> 2), a.B - 1), piece = imin(r & 3, kPieces - 1);
+                const char* p = px + (kPieces * b + piece) * kColBytes + g * 16;
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const int4_t lo = *reinterpret_cast<const int4_t*>(p + m * 128);
+                    const int4_t hi = *reinterpret_cast<const int4_t*>(p + m * 128 + 64);
+                    X[c][m] = int8v_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                }
+                xs[c] = *reinterpret_cast<const uint32_t*>(ps + (b * 4 + g) * 4) -
+                        0x05050505u * (uint32_t)piece;
+            }
+            const bool in = kGroupBlocks * jg + g < C16;
+#pragma unroll 1
+            for (int t = 0; t < ntiles; ++t) {
+                uint32_t w[Q][4], e[Q];
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    unrotate(k.w[i], r, w[i]);
+                    e[i] = k.e[i] ^ 0x80u;
+                    bad |= in && e[i] == 0xffu;
+                    asm volatile("" : "+v"(w[i][0]), "+v"(w[i][1]), "+v"(w[i][2]), "+v"(w[i][3]),
+                                      "+v"(e[i]));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + 1 < ntiles)
+                    load_keys(jg, t + 1, k);
+                else if (more)
+                    load_keys(jg + ka.ksplit, 0, k);
+                __builtin_amdgcn_sched_barrier(0);
+                float4_t acc[CT][2];
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+#define SA_MX_STEP(m)                                                                          \
+    {                                                                                          \
+        const int8v_t W = expand(w[i][m]);                                                     \
+        _Pragma("unroll") for (int c = 0; c < CT; ++c)                                         \
+            acc[c][(m) & 1] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(                \
+                X[c][m], W, i == 0 && (m) < 2 ? float4_t{0.0f, 0.0f, 0.0f, 0.0f}               \
+                                              : acc[c][(m) & 1],                               \
+                0, 4, m, (int)xs[c], 0, (int)e[i]);                                            \
+    }
+                    SA_MX_STEP(0)
+                    SA_MX_STEP(1)
+                    SA_MX_STEP(2)
+                    SA_MX_STEP(3)
+#undef SA_MX_STEP
+                }
+                // a lane's results are the pieces of one (row, batch row)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const float v = ((acc[c][0][2] + acc[c][1][2]) + (acc[c][0][1] + acc[c][1][1])) +
+                                    (acc[c][0][0] + acc[c][1][0]);
+#pragma unroll
+                    for (int u = 0; u < kMaxTiles; ++u)
+                        if (u == t) tot[u][c] += v;
+                }
+            }
+            wave_fence();
+        }
+    }
+
+    // the waves' sums meet in LDS, red[wave][t][c][lane], and are added in wave order
+    const int any_bad = __syncthreads_or(bad != 0);
+    float* red = reinterpret_cast<float*>(lds);
+    constexpr int kVals = kMaxTiles * CT * 64;
+#pragma unroll
+    for (int t = 0; t < kMaxTiles; ++t)
+        if (t < ntiles)
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+                red[wave * kVals + (t * CT + c) * 64 + lane] = tot[t][c];
+    __syncthreads();
+    // outputs of this wave's row set: its ksplit waves take every ksplit-th vector
+    for (int o = ksl; o < ntiles * CT; o += ka.ksplit) {
+        const int t = o / CT, c = o - t * CT;
+        const int row = kTile * (tile0 + t) + r, b = 4 * c + g;
+        const float* v = red + rset * ka.ksplit * kVals + o * 64 + lane;
+        float p[kWaves];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) p[w] = w < ka.ksplit ? v[w * kVals] : 0.0f;
+        float y = p[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) y += p[w];
+        if (row < a.N && b < a.B) {
+            if (any_bad) y = plain_output(a, row, b);
+            if (a.out_half)
+                static_cast<uint16_t*>(a.y)[(int64_t)b * a.N + row] =
+                    __builtin_bit_cast(uint16_t, (_Float16)y);
+            else
+                static_cast<float*>(a.y)[(int64_t)b * a.N + row] = y;
+        }
+    }
+}
+
+template <int CT>
+constexpr int lds_bytes() {
+    const int pieces = kWaves * (kPieces * 4 * CT * kColBytes + 4 * CT * 16);
+    const int red = kWaves * kMaxTiles * CT * 256;
+    return pieces > red ? pieces : red;
+}
+
+template <int Q, int CT, int NP>
+__global__ __launch_bounds__(kThreads, NP == 1 && Q <= 3 ? 4 : 2)
+void k_gemm_mx(KernelArgs a) {
+    __shared__ uint4 lds[(lds_bytes<CT>() + 15) / 16];
+    body<Q, CT, NP>(a, reinterpret_cast<char*>(lds));
+}
+
+struct Geometry {
+    int ct, np, ksplit, sets, tiles, wgs;
+};
+
+Geometry geometry(int q, int N, int K, int B, int target = 0) {
+    Geometry g{};
+    (void)q;
+    const int groups = (K / 128 + kGroupBlocks - 1) / kGroupBlocks;
+    g.ksplit = 1;
+    while (g.ksplit < kWaves && g.ksplit < groups) g.ksplit *= 2;
+    g.ct = (B + 3) / 4;
+    g.np = B <= 2 ? 1 : B <= 4 ? 2 : 4;
+    g.tiles = (N + kTile - 1) / kTile;
+    const int resident = target ? target : 256;
+    g.sets = 1;
+    while (g.sets * g.ksplit < kWaves && g.tiles > resident * g.sets) g.sets *= 2;
+    const int sets = g.sets;
+    int w = (g.tiles + sets - 1) / sets;
+    if (w > resident) w = resident;
+    if ((g.tiles + w * sets - 1) / (w * sets) > kMaxTiles)
+        w = (g.tiles + kMaxTiles * sets - 1) / (kMaxTiles * sets);
+    g.wgs = w;
+    return g;
+}
+
+void set_args(KernelArgs& ka, const Geometry& g) {
+    const uint32_t d = (uint32_t)(ka.a.G / 128);
+    ka.tiles = g.tiles;
+    ka.shares = g.wgs * g.sets;
+    ka.sets = g.sets;
+    ka.ksplit = g.ksplit;
+    ka.NG = ka.a.K / ka.a.G;
+    // J * magic >> 32 = J / d exactly while J * d < 2^32 (takes() bounds K)
+    ka.group_magic = d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
+}
+
+template <int CT, int NP>
+void launch_q(const KernelArgs& ka, int grid, hipStream_t s) {
+    const dim3 g(grid), b(64 * ka.ksplit * ka.sets);
+    switch (ka.a.q) {
+        case 1: hipLaunchKernelGGL((k_gemm_mx<1, CT, NP>), g, b, 0, s, ka); break;
+        case 2: hipLaunchKernelGGL((k_gemm_mx<2, CT, NP>), g, b, 0, s, ka); break;
+        case 3: hipLaunchKernelGGL((k_gemm_mx<3, CT, NP>), g, b, 0, s, ka); break;
+        default: hipLaunchKernelGGL((k_gemm_mx<4, CT, NP>), g, b, 0, s, ka); break;
+    }
+}
+
+void launch_geometry(const KernelArgs& ka, const Geometry& g, hipStream_t s) {
+    if (g.np == 1) launch_q<1, 1>(ka, g.wgs, s);
+    else if (g.np == 2) launch_q<1, 2>(ka, g.wgs, s);
+    else launch_q<2, 4>(ka, g.wgs, s);
+}
+
+}  // namespace
+
+// Batch 2 to 8, up to 4 planes (registers).  A wave's part of the input
+// dimension is 512 columns, so a short K leaves most of a workgroup's waves
+// out, and splitting the activations costs the more the larger the batch:
+// measured against the table kernel (us), batch 4: 3000x768 4.1 against 3.8,
+// 8000x1024 4.5 against 4.2, but 500x1536 4.2 against 4.5 and 28672x512 5.8
+// against 7.5; batch 8: 2000x3072 7.1 against 6.0, 4096x2048 5.7 against 5.8,
+// 12000x1024 7.9 against 7.9, 300x4096 (4 planes) 7.6 against 8.7.
+// The index bounds: 32-bit offsets into a plane's exponents, exact division by
+// multiplication (K).
+bool takes(int q, int N, int K, int G, int B) {
+    if (q > 4 || B < 2 || B > 8 || K % 128 || G % 128 || K > (1 << 22)) return false;
+    if ((int64_t)N * (K / 128) >= (int64_t)1 << 31) return false;
+    if (B <= 4) return K >= 1536 || N >= 12000;
+    return K >= 4096 || (int64_t)N * K >= (int64_t)4096 * 2048;
+}
+
+void launch(const Args& a, hipStream_t s) {
+    KernelArgs ka{};
+    ka.a = a;
+    const Geometry g = geometry(a.q, a.N, a.K, a.B);
+    set_args(ka, g);
+    launch_geometry(ka, g, s);
+}
+
+}  // namespace sa_mx

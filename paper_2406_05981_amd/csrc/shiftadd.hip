@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 
+#include "gemm_mx.h"
 #include "shiftadd.h"
 
 #define SA_VERSION_STRING "0.1.0 gfx950"
@@ -1719,6 +1720,10 @@ int shiftadd_gemm(const uint16_t* x, const uint8_t* packed_bits, const int8_t* e
     const int st = validate_gemm(x, packed_bits, exps, q, N, K, group, batch, y);
     if (st != SA_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (sa_mx::takes(q, N, K, group, batch)) {
+        sa_mx::launch({x, packed_bits, exps, q, N, K, group, batch, y, out_half}, s);
+        return launch_status();
+    }
     sa_plan plan;
     make_plan(q, N, K, group, batch, &plan);
     if (plan.path == 0) {

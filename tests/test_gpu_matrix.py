@@ -1,0 +1,151 @@
+"""GPU parity of the layer's matrix-core forms at the sizes where their tiling
+can go wrong, against the CPU oracle.
+
+Bound: the binary16 form's products are exact and the fp8 split is off by at
+most 2^-24 of the largest of 32 columns per activation, so 32 * 2^-24 of
+sum|terms|; the fp32 additions of one output form chains of at most
+q * K / 128 + 32 terms of which each rounds by 2^-24 of a partial sum."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover - CPU-only environment
+    pytest.skip("no GPU", allow_module_level=True)
+sa = pytest.importorskip("paper_2406_05981_amd.shiftadd")
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def layer(c, exps=None):
+    y = torch.full((c["B"], c["N"]), float("nan"), dtype=torch.float32, device="cuda")
+    sa.sa_shiftadd_gemm(dev(c["x"]), sa.pack_weights(dev(c["signs"])),
+                        dev(c["exps"]) if exps is None else exps, c["q"], c["N"], c["K"], c["G"],
+                        c["B"], y)
+    torch.cuda.synchronize()
+    return y.cpu().numpy().astype(np.float64)
+
+
+def check(y, c, what):
+    y_ref, a_ref = oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], c["G"])
+    bound = (64 + c["q"] * c["K"] / 128) * 2.0 ** -24
+    worst = float((np.abs(y - y_ref) / np.where(a_ref > 0, a_ref, 1)).max())
+    say(f"  {what}: max |y-y_ref|/sum|terms| = {worst:.3e} (bound {bound:.1e})")
+    assert np.isfinite(y).all() and worst <= bound, what
+    assert (y[a_ref == 0] == 0).all(), what
+
+
+# (q, N, K, G, B): partial 512-column groups (1 to 3 blocks), fewer groups than
+# waves, one and several groups a wave, ragged row and 64-row tiles, one and
+# several row tiles a wave, every batch that fills a column tile in part
+SMALL = [
+    (1, 1, 1536, 128, 2), (2, 15, 1664, 128, 3), (3, 16, 1792, 128, 4), (4, 17, 4096, 128, 5),
+    (3, 63, 4224, 128, 6), (2, 65, 4480, 128, 7), (4, 300, 8320, 128, 8), (3, 130, 2304, 768, 3),
+    (1, 4100, 2048, 128, 2), (3, 5000, 4096, 256, 4), (2, 12001, 512, 128, 4),
+    (2, 33000, 640, 128, 8), (1, 40000, 128, 128, 2), (4, 70, 12288, 12288, 8),
+]
+
+
+@pytest.mark.parametrize("q,N,K,G,B", SMALL)
+def test_small_batch(q, N, K, G, B):
+    say(f"matrix form q={q} N={N} K={K} G={G} B={B}")
+    c = workloads.random_case(q, N, K, G, B, seed=31, exp_range=(-12, -3), outlier_fraction=0.01)
+    check(layer(c), c, c["name"])
+
+
+@pytest.mark.parametrize("B", [2, 4, 8])
+def test_activation_ranges(B):
+    """Block maxima from the smallest subnormal to the largest binary16 value,
+    zero blocks, and wide ranges inside one block of 32 columns."""
+    say(f"activation ranges B={B}")
+    c = workloads.random_case(3, 200, 4096, 128, B, seed=32, exp_range=(-10, -2))
+    x = c["x"].astype(np.float64)
+    x[0, :32] = 2.0 ** -24
+    x[0, 32:64] = 0.0
+    x[0, 64:96] *= 2.0 ** -15
+    x[0, 96:128] *= 2.0 ** -10
+    x[0, 96] = 60000.0
+    x[B - 1, 256:288] = np.linspace(-63000, 63000, 32)
+    x[B - 1, 512:1024] *= 1e-6
+    c["x"] = x.astype(np.float16)
+    check(layer(c), c, "ranges")
+    x[1, 2000] = 65504.0
+    x[1, 2001] = -64000.0
+    c["x"] = x.astype(np.float16)
+    check(layer(c), c, "top of the range")
+
+
+@pytest.mark.parametrize("B", [3, 8])
+def test_not_finite_activations(B):
+    """An infinity or NaN reaches every output of its batch row, and no other."""
+    say(f"not finite B={B}")
+    c = workloads.random_case(2, 100, 4096, 128, B, seed=33, exp_range=(-10, -2))
+    x = c["x"].copy()
+    x[0, 700] = np.inf
+    x[1, 5] = np.nan
+    x[2, 9], x[2, 4000] = np.inf, -np.inf
+    ref = oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], 128)[0]
+    c["x"] = x
+    y = layer(c)
+    s = np.where(c["signs"][:, :, 700] > 0, 1.0, -1.0).sum(0)  # two planes: both signs or neither
+    assert np.array_equal(np.isnan(y[0]), s == 0)
+    assert (y[0][s > 0] == np.inf).all() and (y[0][s < 0] == -np.inf).all()
+    assert np.isnan(y[1]).all()
+    p = c["signs"][:, :, 9] * np.array(1, np.int8), -c["signs"][:, :, 4000]
+    t = np.concatenate(p).sum(0)  # four terms of +-inf
+    assert np.array_equal(np.isnan(y[2]), np.abs(t) != 4)
+    assert np.abs(y[3:] - ref[3:]).max(initial=0.0) <= 1e-4 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("B", [2, 7])
+def test_exponent_range(B):
+    """Every int8 exponent, 127 and -128 among them, at an odd address."""
+    say(f"exponent range B={B}")
+    c = workloads.random_case(3, 130, 4096, 128, B, seed=34, exp_range=(-128, 127))
+    c["x"] = (c["x"].astype(np.float64) * 2.0 ** -12).astype(np.float16)
+    flat = c["exps"].reshape(-1)
+    buf = torch.zeros(flat.size + 1, dtype=torch.int8, device="cuda")
+    buf[1:] = dev(flat)
+    check(layer(c, exps=buf[1:]), c, "int8 range")
+    c["exps"] = np.minimum(c["exps"], np.int8(126))
+    check(layer(c), c, "up to 126")
+    c["exps"] = np.clip(c["exps"], -100, -90)
+    check(layer(c), c, "small")
+
+
+@pytest.mark.parametrize("q,N,K,G,B", [(3, 1000, 4096, 128, 4), (2, 70, 4224, 384, 8)])
+def test_half_output_and_graph(q, N, K, G, B):
+    """binary16 outputs are the fp32 ones rounded; replays of a captured call on
+    new activations equal direct calls."""
+    say(f"half output and graph q={q} N={N} K={K} B={B}")
+    c = workloads.random_case(q, N, K, G, B, seed=35, exp_range=(-10, -2))
+    packed, e = sa.pack_weights(dev(c["signs"])), dev(c["exps"])
+    x = dev(c["x"])
+    y32 = torch.empty((B, N), dtype=torch.float32, device="cuda")
+    y16 = torch.empty((B, N), dtype=torch.float16, device="cuda")
+    out = torch.empty((B, N), dtype=torch.float32, device="cuda")
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        sa.sa_shiftadd_gemm(x, packed, e, q, N, K, G, B, out)
+    for rep in range(3):
+        x.copy_(torch.randn((B, K), device="cuda").to(torch.float16))
+        graph.replay()
+        sa.sa_shiftadd_gemm(x, packed, e, q, N, K, G, B, y32)
+        sa.sa_shiftadd_gemm_f16(x, packed, e, q, N, K, G, B, y16)
+        torch.cuda.synchronize()
+        assert torch.equal(out, y32)
+        assert torch.equal(y16, y32.to(torch.float16))
