@@ -16,7 +16,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", name)
-           for name in ("shiftadd.hip", "gemm_mx.hip", "bcq.hip", "alloc.hip")]
+           for name in ("shiftadd.hip", "gemm_mx.hip", "gemm_mfma.hip", "bcq.hip", "alloc.hip")]
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libshiftadd.so")
 ARCH = "gfx950"

@@ -31,6 +31,8 @@
 // 40.8 -> 23.2, batch 8 73.4 -> 30.2; 8192x28672 batch 8 76.2 -> 41.8.
 #include "gemm_mx.h"
 
+#include <type_traits>
+
 #include "shiftadd.h"
 
 namespace sa_mx {
@@ -78,17 +80,30 @@ __device__ inline void unrotate(const uint4 v, int r, uint32_t out[4]) {
     for (int d = 0; d < 4; ++d) out[d] = (s & 8) ? u[(d + 2) & 3] : u[d];
 }
 
-// 32 signs as fp4 (e2m1) +-1.0: register v, nibble n holds bit 4n + v of the word.
-__device__ inline int8v_t expand(uint32_t w) {
+// 32 signs as fp4 (e2m1) +-1.0: register v, nibble n holds bit 4n + v of the
+// word.  A set bit is +1.0 (0010), a clear one -1.0 (1010); the masks of a
+// negated term give the opposite, those of an absent one zero.
+constexpr uint32_t kAnd = 0x88888888u, kXor = 0xAAAAAAAAu, kXorNeg = 0x22222222u;
+
+__device__ inline int8v_t expand(uint32_t w, uint32_t and_mask = kAnd, uint32_t xor_mask = kXor) {
     int8v_t a = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-        a[v] = (int)(((w << (3 - v)) & 0x88888888u) ^ 0xAAAAAAAAu);
+    for (int v = 0; v < 4; ++v) a[v] = (int)(((w << (3 - v)) & and_mask) ^ xor_mask);
     return a;
+}
+
+// T consecutive bytes (exponents or signs of a group's terms), one per byte of
+// the result; 2 and 4 are aligned to their size (checked on the host).
+__device__ inline uint32_t load_terms(const uint8_t* p, int T) {
+    if (T == 4) return *reinterpret_cast<const uint32_t*>(p);
+    if (T == 2) return *reinterpret_cast<const uint16_t*>(p);
+    if (T == 3) return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16);
+    return p[0];
 }
 
 // One output by plain summation, for calls the split does not represent
 // (activations that are not finite, a scale of 2^127).
+template <bool ADD>
 __device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
     const int C = a.K >> 3, NG = a.K / a.G;
     const int T = n >> 6, r = n & 63;
@@ -97,7 +112,7 @@ __device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
 #pragma unroll 1
     for (int i = 0; i < a.q; ++i) {
         const uint8_t* keys = a.packed + ((int64_t)i * a.N + 64 * T) * C + 16 * r;
-        const int8_t* e = a.exps + ((int64_t)i * a.N + n) * NG;
+        const int64_t row = ((int64_t)i * a.N + n) * NG;
         float s = 0.0f;
         int c = 0;
 #pragma unroll 1
@@ -113,7 +128,16 @@ __device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
                     s += (key >> j) & 1 ? x : -x;
                 }
             }
-            y += ldexpf(s, (int)e[g]);
+            if constexpr (ADD) {
+#pragma unroll 1
+                for (int u = 0; u < a.terms; ++u) {
+                    const int sg = a.term_signs[(row + g) * a.terms + u];
+                    const float v = ldexpf(s, (int)a.exps[(row + g) * a.terms + u]);
+                    if (sg) y += sg < 0 ? -v : v;
+                }
+            } else {
+                y += ldexpf(s, (int)a.exps[row + g]);
+            }
         }
     }
     return y;
@@ -139,10 +163,11 @@ __device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
 template <int Q>
 struct Keys {
     uint4 w[Q];
-    uint32_t e[Q];  // exponent byte of this lane's row and block
+    uint32_t e[Q];  // exponent byte of this lane's row and block; additive: T bytes
+    uint32_t s[Q];  // additive: T term signs
 };
 
-template <int Q, int CT, int NP>
+template <int Q, int CT, int NP, bool ADD>
 __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
     const Args& a = ka.a;
     const int lane = threadIdx.x & 63;
@@ -188,8 +213,15 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
         const int T = n >> 6, R = imin(64, a.N - 64 * T);
         const uint32_t off = (uint32_t)(64 * T * C + 16 * (n & 63) + 16 * J * R);
 #pragma unroll
-        for (int i = 0; i < Q; ++i)
-            k.e[i] = (reinterpret_cast<const uint8_t*>(a.exps) + (size_t)i * a.N * NG)[eoff];
+        for (int i = 0; i < Q; ++i) {
+            if constexpr (ADD) {
+                const size_t o = ((size_t)i * a.N * NG + eoff) * a.terms;
+                k.e[i] = load_terms(reinterpret_cast<const uint8_t*>(a.exps) + o, a.terms);
+                k.s[i] = load_terms(reinterpret_cast<const uint8_t*>(a.term_signs) + o, a.terms);
+            } else {
+                k.e[i] = (reinterpret_cast<const uint8_t*>(a.exps) + (size_t)i * a.N * NG)[eoff];
+            }
+        }
 #pragma unroll
         for (int i = 0; i < Q; ++i)
             k.w[i] = *reinterpret_cast<const uint4*>(a.packed + (size_t)i * a.N * C + off);
@@ -303,12 +335,18 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
             const bool in = kGroupBlocks * jg + g < C16;
 #pragma unroll 1
             for (int t = 0; t < ntiles; ++t) {
-                uint32_t w[Q][4], e[Q];
+                uint32_t w[Q][4], e[Q], sg[Q];
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
                     unrotate(k.w[i], r, w[i]);
-                    e[i] = k.e[i] ^ 0x80u;
-                    bad |= in && e[i] == 0xffu;
+                    if constexpr (ADD) {
+                        e[i] = k.e[i];
+                        sg[i] = k.s[i];
+                        asm volatile("" : "+v"(sg[i]));
+                    } else {
+                        e[i] = k.e[i] ^ 0x80u;
+                        bad |= in && e[i] == 0xffu;
+                    }
                     asm volatile("" : "+v"(w[i][0]), "+v"(w[i][1]), "+v"(w[i][2]), "+v"(w[i][3]),
                                       "+v"(e[i]));
                 }
@@ -319,22 +357,40 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                     load_keys(jg + ka.ksplit, 0, k);
                 __builtin_amdgcn_sched_barrier(0);
                 float4_t acc[CT][2];
+                auto step = [&](auto mc, const int8v_t W, uint32_t es) {
+                    constexpr int m = decltype(mc)::value;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        acc[c][m & 1] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                            X[c][m], W, acc[c][m & 1], 0, 4, m, (int)xs[c], 0, (int)es);
+                };
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    acc[c][0] = acc[c][1] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-#define SA_MX_STEP(m)                                                                          \
-    {                                                                                          \
-        const int8v_t W = expand(w[i][m]);                                                     \
-        _Pragma("unroll") for (int c = 0; c < CT; ++c)                                         \
-            acc[c][(m) & 1] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(                \
-                X[c][m], W, i == 0 && (m) < 2 ? float4_t{0.0f, 0.0f, 0.0f, 0.0f}               \
-                                              : acc[c][(m) & 1],                               \
-                0, 4, m, (int)xs[c], 0, (int)e[i]);                                            \
-    }
-                    SA_MX_STEP(0)
-                    SA_MX_STEP(1)
-                    SA_MX_STEP(2)
-                    SA_MX_STEP(3)
-#undef SA_MX_STEP
+                    if constexpr (ADD) {
+                        // a term's sign goes into the expansion: no term, no weight
+#pragma unroll 1
+                        for (int u = 0; u < a.terms; ++u) {
+                            const int s8 = (int)(int8_t)sg[i];
+                            const uint32_t es = s8 ? (e[i] & 0xffu) ^ 0x80u : 0x80u;
+                            const uint32_t am = s8 ? kAnd : 0u;
+                            const uint32_t xm8 = s8 ? (s8 < 0 ? kXorNeg : kXor) : 0u;
+                            bad |= in && es == 0xffu;
+                            step(std::integral_constant<int, 0>{}, expand(w[i][0], am, xm8), es);
+                            step(std::integral_constant<int, 1>{}, expand(w[i][1], am, xm8), es);
+                            step(std::integral_constant<int, 2>{}, expand(w[i][2], am, xm8), es);
+                            step(std::integral_constant<int, 3>{}, expand(w[i][3], am, xm8), es);
+                            e[i] >>= 8;
+                            sg[i] >>= 8;
+                        }
+                    } else {
+                        step(std::integral_constant<int, 0>{}, expand(w[i][0]), e[i]);
+                        step(std::integral_constant<int, 1>{}, expand(w[i][1]), e[i]);
+                        step(std::integral_constant<int, 2>{}, expand(w[i][2]), e[i]);
+                        step(std::integral_constant<int, 3>{}, expand(w[i][3]), e[i]);
+                    }
                 }
                 // a lane's results are the pieces of one (row, batch row)
 #pragma unroll
@@ -373,7 +429,7 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) y += p[w];
         if (row < a.N && b < a.B) {
-            if (any_bad) y = plain_output(a, row, b);
+            if (any_bad) y = plain_output<ADD>(a, row, b);
             if (a.out_half)
                 static_cast<uint16_t*>(a.y)[(int64_t)b * a.N + row] =
                     __builtin_bit_cast(uint16_t, (_Float16)y);
@@ -390,11 +446,10 @@ constexpr int lds_bytes() {
     return pieces > red ? pieces : red;
 }
 
-template <int Q, int CT, int NP>
-__global__ __launch_bounds__(kThreads, NP == 1 && Q <= 3 ? 4 : 2)
-void k_gemm_mx(KernelArgs a) {
+template <int Q, int CT, int NP, bool ADD>
+__global__ __launch_bounds__(kThreads, 2) void k_gemm_mx(KernelArgs a) {
     __shared__ uint4 lds[(lds_bytes<CT>() + 15) / 16];
-    body<Q, CT, NP>(a, reinterpret_cast<char*>(lds));
+    body<Q, CT, NP, ADD>(a, reinterpret_cast<char*>(lds));
 }
 
 struct Geometry {
@@ -433,21 +488,22 @@ void set_args(KernelArgs& ka, const Geometry& g) {
     ka.group_magic = d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
 }
 
-template <int CT, int NP>
+template <int CT, int NP, bool ADD>
 void launch_q(const KernelArgs& ka, int grid, hipStream_t s) {
     const dim3 g(grid), b(64 * ka.ksplit * ka.sets);
     switch (ka.a.q) {
-        case 1: hipLaunchKernelGGL((k_gemm_mx<1, CT, NP>), g, b, 0, s, ka); break;
-        case 2: hipLaunchKernelGGL((k_gemm_mx<2, CT, NP>), g, b, 0, s, ka); break;
-        case 3: hipLaunchKernelGGL((k_gemm_mx<3, CT, NP>), g, b, 0, s, ka); break;
-        default: hipLaunchKernelGGL((k_gemm_mx<4, CT, NP>), g, b, 0, s, ka); break;
+        case 1: hipLaunchKernelGGL((k_gemm_mx<1, CT, NP, ADD>), g, b, 0, s, ka); break;
+        case 2: hipLaunchKernelGGL((k_gemm_mx<2, CT, NP, ADD>), g, b, 0, s, ka); break;
+        case 3: hipLaunchKernelGGL((k_gemm_mx<3, CT, NP, ADD>), g, b, 0, s, ka); break;
+        default: hipLaunchKernelGGL((k_gemm_mx<4, CT, NP, ADD>), g, b, 0, s, ka); break;
     }
 }
 
+template <bool ADD>
 void launch_geometry(const KernelArgs& ka, const Geometry& g, hipStream_t s) {
-    if (g.np == 1) launch_q<1, 1>(ka, g.wgs, s);
-    else if (g.np == 2) launch_q<1, 2>(ka, g.wgs, s);
-    else launch_q<2, 4>(ka, g.wgs, s);
+    if (g.np == 1) launch_q<1, 1, ADD>(ka, g.wgs, s);
+    else if (g.np == 2) launch_q<1, 2, ADD>(ka, g.wgs, s);
+    else launch_q<2, 4, ADD>(ka, g.wgs, s);
 }
 
 }  // namespace
@@ -473,7 +529,8 @@ void launch(const Args& a, hipStream_t s) {
     ka.a = a;
     const Geometry g = geometry(a.q, a.N, a.K, a.B);
     set_args(ka, g);
-    launch_geometry(ka, g, s);
+    if (a.terms) launch_geometry<true>(ka, g, s);
+    else launch_geometry<false>(ka, g, s);
 }
 
 }  // namespace sa_mx

@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 
+#include "gemm_mfma.h"
 #include "gemm_mx.h"
 #include "shiftadd.h"
 
@@ -1721,7 +1722,11 @@ int shiftadd_gemm(const uint16_t* x, const uint8_t* packed_bits, const int8_t* e
     if (st != SA_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (sa_mx::takes(q, N, K, group, batch)) {
-        sa_mx::launch({x, packed_bits, exps, q, N, K, group, batch, y, out_half}, s);
+        sa_mx::launch({x, packed_bits, exps, nullptr, q, N, K, group, batch, 0, y, out_half}, s);
+        return launch_status();
+    }
+    if (sa_mfma::takes(q, N, K, group, batch, false)) {
+        sa_mfma::launch({x, packed_bits, exps, nullptr, q, N, K, group, batch, 0, y, out_half}, s);
         return launch_status();
     }
     sa_plan plan;
@@ -1930,9 +1935,17 @@ SA_API int sa_shiftadd_gemm_terms(const uint16_t* x, const uint8_t* packed_bits,
     const uintptr_t al = terms == 2 ? 1u : (terms == 4 ? 3u : 0u);
     if ((reinterpret_cast<uintptr_t>(exps) & al) || (reinterpret_cast<uintptr_t>(term_signs) & al))
         return SA_ERR_ALIGN;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (sa_mx::takes(q, N, K, group, batch)) {
+        sa_mx::launch({x, packed_bits, exps, term_signs, q, N, K, group, batch, terms, y, 0}, s);
+        return launch_status();
+    }
+    if (sa_mfma::takes(q, N, K, group, batch, true)) {
+        sa_mfma::launch({x, packed_bits, exps, term_signs, q, N, K, group, batch, terms, y, 0}, s);
+        return launch_status();
+    }
     sa_plan plan;
     make_plan(q, N, K, group, batch, &plan);  // row kernel (batch 1) or batch kernel
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (plan.path == 2) {
         BatchArgs a{};
         a.x = x;

@@ -65,6 +65,80 @@ def test_small_batch(q, N, K, G, B):
     check(layer(c), c, c["name"])
 
 
+# larger batches, columns shared by waves: 1 to 4 row tiles, fewer groups than
+# waves, a partial last group, several groups a wave, ragged rows and batch;
+# then activations shared in LDS: 1, 2 and 4 column tiles, 4 and 2 row tiles,
+# ragged everything, a last group of one block
+LARGE = [
+    (3, 4090, 4096, 128, 16), (4, 4096, 4224, 128, 16), (3, 4097, 8320, 128, 15), (3, 4100, 4096, 128, 32),
+    (3, 6001, 4096, 256, 30), (1, 9000, 4096, 128, 13), (3, 4096, 4096, 128, 64),
+    (2, 12001, 2176, 128, 16), (2, 8000, 4480, 640, 17), (4, 5000, 4096, 4096, 20),
+    (2, 700, 2176, 128, 256), (2, 12001, 1152, 128, 16), (2, 2100, 4224, 384, 129),
+    (1, 3001, 1280, 128, 256), (3, 2000, 640, 128, 255), (4, 8001, 512, 128, 60),
+    (3, 2300, 2048, 256, 250), (4, 4100, 1664, 128, 130), (2, 11007, 1024, 1024, 128),
+    (3, 63, 4096, 128, 250),
+]
+
+
+@pytest.mark.parametrize("q,N,K,G,B", LARGE)
+def test_large_batch(q, N, K, G, B):
+    say(f"matrix form q={q} N={N} K={K} G={G} B={B}")
+    c = workloads.random_case(q, N, K, G, B, seed=36, exp_range=(-12, -3), outlier_fraction=0.01)
+    check(layer(c), c, c["name"])
+
+
+def terms_layer(c, shift=0):
+    y = torch.full((c["B"], c["N"]), float("nan"), dtype=torch.float32, device="cuda")
+    e, s = dev(c["exps"]).reshape(-1), dev(c["term_signs"]).reshape(-1)
+    if shift:  # 2-byte aligned, not 8-byte
+        be = torch.zeros(e.numel() + shift, dtype=torch.int8, device="cuda")
+        bs = torch.zeros_like(be)
+        be[shift:], bs[shift:] = e, s
+        e, s = be[shift:], bs[shift:]
+    sa.sa_shiftadd_gemm_terms(dev(c["x"]), sa.pack_weights(dev(c["signs"])), e, s, c["q"], c["N"],
+                              c["K"], c["G"], c["T"], c["B"], y)
+    torch.cuda.synchronize()
+    return y.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("q,N,K,G,B,T,shift", [
+    (3, 1000, 4096, 128, 4, 2, 0), (4, 300, 4224, 384, 8, 3, 0), (2, 5000, 1664, 128, 2, 4, 4),
+    (1, 4100, 8320, 128, 7, 1, 1),
+    (2, 4096, 4096, 128, 16, 2, 0), (2, 4100, 4096, 128, 16, 2, 2), (3, 8200, 4224, 128, 16, 2, 0),
+    (1, 12001, 4096, 256, 33, 3, 0), (4, 8200, 4096, 128, 16, 1, 0), (2, 12000, 2048, 128, 16, 4, 0)])
+def test_additive(q, N, K, G, B, T, shift):
+    say(f"additive matrix form q={q} N={N} K={K} G={G} B={B} T={T} shift={shift}")
+    c = workloads.terms_case(q, N, K, G, B, T, seed=37)
+    c["exps"][0, 0, 0, -1], c["term_signs"][0, 0, 0, -1] = 127, 0  # no term, whatever its exponent
+    y_ref, a_ref = oracle.shiftadd_gemm_terms(c["x"], c["signs"], c["exps"], c["term_signs"], G)
+    bound = (64 + T * q * K / 128) * 2.0 ** -24
+    y = terms_layer(c, shift)
+    worst = float((np.abs(y - y_ref) / a_ref).max())
+    say(f"  max |y-y_ref|/sum|terms| = {worst:.3e} (bound {bound:.1e})")
+    assert np.isfinite(y).all() and worst <= bound
+
+
+@pytest.mark.parametrize("q,N,K,B", [(2, 4096, 4096, 16), (2, 2300, 2048, 250)])
+def test_large_batch_extremes(q, N, K, B):
+    """Not finite activations, subnormals, the int8 range of exponents."""
+    say(f"large batch extremes q={q} N={N} K={K} B={B}")
+    c = workloads.random_case(q, N, K, 128, B, seed=38, exp_range=(-128, 127))
+    x = c["x"].astype(np.float64) * 2.0 ** -12
+    x[3] = 2.0 ** -24
+    c["x"] = x.astype(np.float16)
+    check(layer(c), c, "int8 range, subnormals")
+    c["exps"] = np.clip(c["exps"], -10, -3)
+    ref = oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], 128)[0]
+    c["x"][0, 5] = np.nan
+    c["x"][1, 700] = np.inf
+    y = layer(c)
+    s = np.where(c["signs"][:, :, 700] > 0, 1.0, -1.0).sum(0)
+    assert np.isnan(y[0]).all()
+    assert np.array_equal(np.isnan(y[1]), s == 0) and np.isinf(y[1][s != 0]).all()
+    assert np.array_equal(y[1][s != 0] > 0, s[s != 0] > 0)
+    assert np.abs(y[2:] - ref[2:]).max() <= 1e-5 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("B", [2, 4, 8])
 def test_activation_ranges(B):
     """Block maxima from the smallest subnormal to the largest binary16 value,
@@ -125,7 +199,8 @@ def test_exponent_range(B):
     check(layer(c), c, "small")
 
 
-@pytest.mark.parametrize("q,N,K,G,B", [(3, 1000, 4096, 128, 4), (2, 70, 4224, 384, 8)])
+@pytest.mark.parametrize("q,N,K,G,B", [(3, 1000, 4096, 128, 4), (2, 70, 4224, 384, 8),
+                                       (3, 4090, 4096, 128, 16), (2, 2300, 2048, 128, 250)])
 def test_half_output_and_graph(q, N, K, G, B):
     """binary16 outputs are the fp32 ones rounded; replays of a captured call on
     new activations equal direct calls."""
