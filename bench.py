@@ -832,6 +832,11 @@ def main() -> int:
         log(f"read floor: {read_floor}")
 
     kernel = KERNELS[plan["path"]]
+    # the plan describes the table kernels; the library picks a matrix-core kernel
+    # for most row-wise and additive batches of up to 4 planes
+    label = kernel
+    if plan["path"] in (2, "add2") and q <= 4:
+        label = f"matrix cores (k_gemm_mx, k_gemm_split, k_gemm_tile); short layers {kernel}"
     traffic = measured_traffic(kernel + (f"_t{terms}" if terms else ""), args.workload,
                                args.layer, B)
     out = {
@@ -861,7 +866,7 @@ def main() -> int:
                        f"row-wise, group {G}"),
             "weight_copies": copies,
             "launch": "eager" if args.eager else "hip graph replay",
-            "kernel": kernel,
+            "kernel": label,
             "rows_per_workgroup": plan["rows_per_wg"],
             "workgroups": plan["workgroups"],
         },
