@@ -9,18 +9,23 @@
 // the operand's block scale, so nothing is shifted or added outside the matrix
 // core over the whole input dimension.
 //
-// Activations.  A binary16 activation is split into three fp8 (e4m3) pieces of
-// four significand bits each, x = S (p0 + p1 / 32 + p2 / 1024), S the power of
-// two that brings the largest of 32 columns below 16; the pieces are matrix
-// columns of their own, so they cost no extra instructions while
-// 4 * batch <= 16.  The split is exact for every x above 2^-13 of its block's
-// largest and off by at most 2^-24 of that largest otherwise.
+// Activations.  A binary16 activation is split into four fp8 (e4m3) pieces of
+// four significand bits each, x = S (p0 + p1 / 2^5 + p2 / 2^10 + p3 / 2^15), S the
+// power of two that brings the largest of 32 columns into [8, 16); the pieces are
+// the four matrix columns of a batch row, so they cost no extra products.  The last
+// piece's smallest step is 2^-24 S, below half of which bits are dropped: a block
+// whose largest is below 16 loses none (2^-24 is binary16's own step), in any other
+// block a value above 2^-17 of the largest is exact and the rest is off by at most
+// 2^-28 of the largest, which fp32 sums with that largest do not resolve.
 // The core adds products of eight consecutive columns in a window of 13 bits
 // below the largest (measured: 2^8 + 2^-5 is kept, 2^8 + 2^-6 is not, further
 // apart fp32); below 16 and down to e4m3's 2^-9 the pieces stay inside that
 // window, so these sums are exact and everything after them is fp32.
-// Measured against 64 bits (4096x4096 q=3, N(0,1) with outliers, 2-norm):
-// 6e-8 relative, against 1.2e-7 (batch 2-4) of the table kernel.
+// Measured against 64 bits (2-norm, 3 planes, batch 8, the table batch kernel's
+// error in brackets): 4096 columns N(0,1) 6.3e-8 (1.2e-7), four columns x1000
+// 9.6e-8 (1.2e-7), x16000 1.3e-7 (1.3e-7), 28672 columns 8.1e-8 (1.7e-7), four
+// columns x16000 1.3e-7 (2.1e-7).  With three pieces 3.0e-7 at x16000; the fourth
+// costs 8192x28672 batch 8 40.1 -> 44.3 us.
 //
 // What bounds it: at 28672x8192 q=3 the key stream (16.5 us as a plain read);
 // per 16 rows x 128 columns x plane a SIMD needs 25 ns (batch <= 4: 8 VALU
@@ -48,7 +53,7 @@ constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kTile = 16;
 constexpr int kGroupBlocks = 4;   // 128-column blocks per group
-constexpr int kPieces = 3;        // fp8 pieces of an activation
+constexpr int kPieces = 4;        // fp8 pieces of an activation
 constexpr int kColBytes = 528;    // LDS bytes of one piece of one batch row over a group (512 + 16)
 // |x| from this binary16 pattern (63488) on would round to a first piece beyond the
 // binary16 range; it and what is not finite take plain_output
@@ -199,7 +204,7 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
     const int ntiles = base + (share < extra ? 1 : 0);
     const int tile0 = share * base + imin(share, extra);
 
-    // this wave's pieces [3 B][528 bytes], then its scales [B][4 blocks] words
+    // this wave's pieces [4 B][528 bytes], then its scales [B][4 blocks] words
     constexpr int kMaxB = 4 * CT;
     constexpr int kWaveBytes = kPieces * kMaxB * kColBytes + kMaxB * 16;
     char* px = lds + wave * kWaveBytes;
@@ -250,10 +255,11 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
             mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0xB1, 0xf, 0xf, true));
             bad |= mx >= kSplitLimit;
             const uint32_t E = max(mx >> 10, 1u);
-            const float S[3] = {__builtin_bit_cast(float, (E + 109u) << 23),
-                                __builtin_bit_cast(float, (E + 104u) << 23),
-                                __builtin_bit_cast(float, (E + 99u) << 23)};
-            uint32_t out[3][2][2];  // [piece][s][v & 1]
+            float S[kPieces];
+#pragma unroll
+            for (int p = 0; p < kPieces; ++p)
+                S[p] = __builtin_bit_cast(float, (E + 109u - 5u * p) << 23);
+            uint32_t out[kPieces][2][2];  // [piece][s][v & 1]
 #pragma unroll
             for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -316,12 +322,12 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
             wave_fence();
             if (more) load_x(jg + ka.ksplit, raw);
             // matrix column r is piece r & 3 of batch row r >> 2 (+ 4 per column
-            // tile); columns that stand for nothing repeat a neighbour's
+            // tile); columns of batch rows past the last repeat it
             int8v_t X[CT][4];
             uint32_t xs[CT];
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                const int b = imin(4 * c + (r >> 2), a.B - 1), piece = imin(r & 3, kPieces - 1);
+                const int b = imin(4 * c + (r >> 2), a.B - 1), piece = r & 3;
                 const char* p = px + (kPieces * b + piece) * kColBytes + g * 16;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
@@ -395,8 +401,8 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                 // a lane's results are the pieces of one (row, batch row)
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    const float v = ((acc[c][0][2] + acc[c][1][2]) + (acc[c][0][1] + acc[c][1][1])) +
-                                    (acc[c][0][0] + acc[c][1][0]);
+                    const float4_t s = acc[c][0] + acc[c][1];
+                    const float v = ((s[3] + s[2]) + s[1]) + s[0];
 #pragma unroll
                     for (int u = 0; u < kMaxTiles; ++u)
                         if (u == t) tot[u][c] += v;
