@@ -55,9 +55,6 @@ constexpr int kTile = 16;
 constexpr int kGroupBlocks = 4;   // 128-column blocks per group
 constexpr int kPieces = 4;        // fp8 pieces of an activation
 constexpr int kColBytes = 528;    // LDS bytes of one piece of one batch row over a group (512 + 16)
-// |x| from this binary16 pattern (63488) on would round to a first piece beyond the
-// binary16 range; it and what is not finite take plain_output
-constexpr uint32_t kSplitLimit = 0x7bc0u;
 constexpr int kMaxTiles = 8;      // row tiles of one wave
 
 __host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
@@ -106,7 +103,7 @@ __device__ inline uint32_t load_terms(const uint8_t* p, int T) {
     return p[0];
 }
 
-// One output by plain summation, for calls the split does not represent
+// One output by plain summation, for what the matrix core does not take
 // (activations that are not finite, a scale of 2^127).
 template <bool ADD>
 __device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
@@ -253,12 +250,23 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
             uint32_t mx = __builtin_bit_cast(uint32_t, hm);
             mx = max(mx & 0x7fffu, (mx >> 16) & 0x7fffu);
             mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0xB1, 0xf, 0xf, true));
-            bad |= mx >= kSplitLimit;
+            bad |= mx >= 0x7c00u;
             const uint32_t E = max(mx >> 10, 1u);
+            // From 63488 on the first piece would round up past the binary16 range: a
+            // block in the top binade is halved (exact but for subnormals, far below
+            // the last piece's step) and only its scale byte keeps the exponent.
+            if (__any(E >= 30u)) {
+                const _Float16 f = E >= 30u ? (_Float16)0.5f : (_Float16)1.0f;
+                const half2_t h = {f, f};
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    d[u] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, d[u]) * h);
+            }
+            const uint32_t F = min(E, 29u);
             float S[kPieces];
 #pragma unroll
             for (int p = 0; p < kPieces; ++p)
-                S[p] = __builtin_bit_cast(float, (E + 109u - 5u * p) << 23);
+                S[p] = __builtin_bit_cast(float, (F + 109u - 5u * p) << 23);
             uint32_t out[kPieces][2][2];  // [piece][s][v & 1]
 #pragma unroll
             for (int s = 0; s < 2; ++s)

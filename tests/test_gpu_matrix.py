@@ -280,3 +280,23 @@ def test_massive_outliers(B, outlier):
     e, er = norm_error(layer(c), ref), norm_error(table_batch(c), ref)
     say(f"  error {e:.3e}, table kernel {er:.3e}")
     assert e <= 1.1 * er
+
+
+@pytest.mark.parametrize("q,N,K,G,B", [(3, 200, 4096, 128, 2), (3, 200, 4096, 4096, 4),
+                                       (2, 3000, 8192, 128, 8)])
+def test_top_of_the_range_leaves_other_rows(q, N, K, G, B):
+    """Finite activations of any size run the same arithmetic: the other batch
+    rows keep their bits, and the row itself is a layer like any other."""
+    say(f"top of the range q={q} N={N} K={K} G={G} B={B}")
+    c = workloads.random_case(q, N, K, G, B, seed=55, exp_range=(-10, -3))
+    clean = layer(c)
+    c["x"][1, 100], c["x"][1, K - 1], c["x"][1, 64:96] = 65504.0, -63500.0, np.float16(63488.0)
+    y = layer(c)
+    others = [b for b in range(B) if b != 1]
+    assert np.array_equal(y[others], clean[others])
+    check(y, c, "top of the range")
+    # 2^15 times a row of ordinary values is 2^15 times its result, bit for bit
+    c["x"][0] = np.clip(c["x"][0], -1.999, 1.999)
+    small = layer(c)[0]
+    c["x"][0] = (c["x"][0].astype(np.float64) * 2.0 ** 15).astype(np.float16)
+    assert np.array_equal(layer(c)[0], small * 2.0 ** 15)
