@@ -56,6 +56,13 @@ constexpr int kGroupBlocks = 4;   // 128-column blocks per group
 constexpr int kPieces = 4;        // fp8 pieces of an activation
 constexpr int kColBytes = 528;    // LDS bytes of one piece of one batch row over a group (512 + 16)
 constexpr int kMaxTiles = 8;      // row tiles of one wave
+// Factors above 2^100 (scale bytes above this one): sums over 512 columns and 4
+// planes of |x| < 2^16 may leave fp32 before their terms cancel, and the byte of
+// 2^127 is a NaN.  A wave that meets one runs its columns a second time for these
+// factors alone, with activations scaled by 2^-kTopShift (28672x8192 q=3 batch 8:
+// 43 us with one such factor, 64 us with exponents over all of int8, 34 without).
+constexpr uint32_t kTopByte = 228;
+constexpr int kTopShift = 64;
 
 __host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
 
@@ -103,8 +110,7 @@ __device__ inline uint32_t load_terms(const uint8_t* p, int T) {
     return p[0];
 }
 
-// One output by plain summation, for what the matrix core does not take
-// (activations that are not finite, a scale of 2^127).
+// One output by plain summation, for activations that are not finite.
 template <bool ADD>
 __device__ __forceinline__ float plain_output(const Args& a, int n, int b) {
     const int C = a.K >> 3, NG = a.K / a.G;
@@ -228,7 +234,7 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
         for (int i = 0; i < Q; ++i)
             k.w[i] = *reinterpret_cast<const uint4*>(a.packed + (size_t)i * a.N * C + off);
     };
-    uint32_t bad = 0;  // an activation that is not finite, or a scale of 2^127
+    uint32_t bad = 0;  // an activation that is not finite
     auto split_x = [&](int jg) {
         const bool in = kGroupBlocks * jg + xp < C16;
         const bool short_group = kGroupBlocks * (jg + 1) > C16;  // uniform
@@ -319,9 +325,19 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) tot[t][c] = 0.0f;
 
-    if (ksl < groups && ntiles > 0) {
+    uint32_t top = 0;  // the largest scale byte
+    const int passes = ksl < groups && ntiles > 0 ? 2 : 0;
+#pragma unroll 1
+    for (int pass = 0; pass < passes; ++pass) {
         Keys<Q> k;
-        load_keys(ksl, 0, k);
+        int jg0 = ksl, t0 = 0;
+        // opaque: the addresses of the first loads are not kept over the passes
+        asm volatile("" : "+s"(jg0), "+s"(t0));
+        if (pass) {
+            if (!__any(top > kTopByte)) break;
+            load_x(jg0, raw);
+        }
+        load_keys(jg0, t0, k);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll 1
         for (int jg = ksl; jg < groups; jg += ka.ksplit) {
@@ -344,9 +360,16 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                     X[c][m] = int8v_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                 }
                 xs[c] = *reinterpret_cast<const uint32_t*>(ps + (b * 4 + g) * 4) -
-                        0x05050505u * (uint32_t)piece;
+                        0x05050505u * (uint32_t)piece -
+                        0x01010101u * (uint32_t)(pass * kTopShift);
             }
-            const bool in = kGroupBlocks * jg + g < C16;
+            // The scale byte of a factor in this pass.  In the other pass its byte is 0:
+            // 2^-127 of its product beside the product itself, and nothing at all with
+            // the activations of the second pass.
+            auto scale = [&](uint32_t es) {
+                top = max(top, es);
+                return (es > kTopByte) == (pass != 0) ? es - (uint32_t)pass : 0u;
+            };
 #pragma unroll 1
             for (int t = 0; t < ntiles; ++t) {
                 uint32_t w[Q][4], e[Q], sg[Q];
@@ -354,12 +377,11 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                 for (int i = 0; i < Q; ++i) {
                     unrotate(k.w[i], r, w[i]);
                     if constexpr (ADD) {
-                        e[i] = k.e[i];
+                        e[i] = k.e[i] ^ 0x80808080u;
                         sg[i] = k.s[i];
                         asm volatile("" : "+v"(sg[i]));
                     } else {
-                        e[i] = k.e[i] ^ 0x80u;
-                        bad |= in && e[i] == 0xffu;
+                        e[i] = scale(k.e[i] ^ 0x80u);
                     }
                     asm volatile("" : "+v"(w[i][0]), "+v"(w[i][1]), "+v"(w[i][2]), "+v"(w[i][3]),
                                       "+v"(e[i]));
@@ -388,10 +410,9 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
 #pragma unroll 1
                         for (int u = 0; u < a.terms; ++u) {
                             const int s8 = (int)(int8_t)sg[i];
-                            const uint32_t es = s8 ? (e[i] & 0xffu) ^ 0x80u : 0x80u;
+                            const uint32_t es = scale(s8 ? e[i] & 0xffu : 0x80u);
                             const uint32_t am = s8 ? kAnd : 0u;
                             const uint32_t xm8 = s8 ? (s8 < 0 ? kXorNeg : kXor) : 0u;
-                            bad |= in && es == 0xffu;
                             step(std::integral_constant<int, 0>{}, expand(w[i][0], am, xm8), es);
                             step(std::integral_constant<int, 1>{}, expand(w[i][1], am, xm8), es);
                             step(std::integral_constant<int, 2>{}, expand(w[i][2], am, xm8), es);
@@ -410,7 +431,8 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
                     const float4_t s = acc[c][0] + acc[c][1];
-                    const float v = ((s[3] + s[2]) + s[1]) + s[0];
+                    float v = ((s[3] + s[2]) + s[1]) + s[0];
+                    if (pass) v = ldexpf(v, kTopShift + 1);
 #pragma unroll
                     for (int u = 0; u < kMaxTiles; ++u)
                         if (u == t) tot[u][c] += v;

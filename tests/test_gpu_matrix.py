@@ -300,3 +300,47 @@ def test_top_of_the_range_leaves_other_rows(q, N, K, G, B):
     small = layer(c)[0]
     c["x"][0] = (c["x"][0].astype(np.float64) * 2.0 ** 15).astype(np.float16)
     assert np.array_equal(layer(c)[0], small * 2.0 ** 15)
+
+
+@pytest.mark.parametrize("B", [2, 3, 8])
+@pytest.mark.parametrize("T", [0, 2])
+def test_sums_that_cancel_before_the_shift(B, T):
+    """A group's sum is small where its terms cancel: nothing overflows before the
+    factor, up to 2^126, is applied."""
+    say(f"cancelling group B={B} T={T}")
+    q, N, K = 2, 50, 4096
+    x = np.zeros((B, K))
+    x[:, 128:192], x[:, 192:256], x[:, 255] = 4.0, -4.0, -3.75
+    x[:, 1000] = 1.0
+    signs = np.ones((q, N, K), np.int8)
+    signs[:, :, 1000] = np.where(np.arange(N) % 2, 1, -1)
+    exps = np.zeros((q, N, K // 128), np.int8)
+    exps[0, :, 1] = np.arange(126 - N + 1, 127)
+    c = dict(x=x.astype(np.float16), signs=signs, exps=exps, q=q, N=N, K=K, G=128, B=B)
+    if T:
+        ts = np.ones((q, N, K // 128, T), np.int8)
+        ts[..., 1] = 0  # no second term, whatever its exponent
+        c.update(T=T, exps=np.stack([exps, np.full_like(exps, 127)], -1), term_signs=ts)
+        y = terms_layer(c)
+        ref = oracle.shiftadd_gemm_terms(c["x"], signs, c["exps"], ts, 128)[0]
+    else:
+        y, ref = layer(c), oracle.shiftadd_gemm(c["x"], signs, exps, 128)[0]
+    assert np.array_equal(y, ref.astype(np.float32).astype(np.float64))
+
+
+@pytest.mark.parametrize("B", [2, 8, 16, 250])
+def test_smallest_exponents(B):
+    """Results about 2^-126 keep the spacing 2^-149 of fp32 subnormals, also where
+    one row of the same tile has the largest factor."""
+    say(f"smallest exponents B={B}")
+    q, N, K = 3, {16: 4096, 250: 2300}.get(B, 200), 4096
+    c = workloads.random_case(q, N, K, 128, B, seed=58, exp_range=(-128, -124))
+    c["x"] = (c["x"].astype(np.float64) * 2.0 ** -9).astype(np.float16)
+    for row in (None, 33):
+        if row is not None:
+            c["exps"][0, row, 7] = 127
+        y, (ref, a_ref) = layer(c), oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], 128)
+        # one rounding per plane and 128 columns, to fp32 or to a multiple of 2^-149
+        bound = (64 + q * K / 128) * 2.0 ** -24 * a_ref + q * K / 128 * 2.0 ** -149
+        say(f"  max |y-y_ref| / bound = {(np.abs(y - ref) / bound).max():.2e}")
+        assert (np.abs(y - ref) <= bound).all()
