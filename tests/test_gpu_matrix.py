@@ -344,3 +344,40 @@ def test_smallest_exponents(B):
         bound = (64 + q * K / 128) * 2.0 ** -24 * a_ref + q * K / 128 * 2.0 ** -149
         say(f"  max |y-y_ref| / bound = {(np.abs(y - ref) / bound).max():.2e}")
         assert (np.abs(y - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("q,N,K,G,B,T", [(3, 200, 4096, 128, 2, 0), (2, 200, 4096, 4096, 4, 0),
+                                         (1, 3000, 8192, 128, 8, 0), (2, 40000, 128, 128, 2, 0),
+                                         (2, 300, 4224, 384, 7, 3)])
+def test_not_finite_leaves_other_rows(q, N, K, G, B, T):
+    """Infinities and NaNs of a batch row reach its outputs as the oracle says
+    (absent terms take none); the other rows keep their bits."""
+    say(f"not finite, other rows q={q} N={N} K={K} G={G} B={B} T={T}")
+    if T:
+        c = workloads.terms_case(q, N, K, G, B, T, seed=56)
+        c["term_signs"][:, ::2, 0] = 0
+    else:
+        c = workloads.random_case(q, N, K, G, B, seed=56, exp_range=(-10, -3))
+
+    def both():
+        with np.errstate(invalid="ignore"):
+            if T:
+                return terms_layer(c), oracle.shiftadd_gemm_terms(c["x"], c["signs"], c["exps"],
+                                                                  c["term_signs"], G)[0]
+            return layer(c), oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], G)[0]
+
+    clean = both()[0]
+    c["x"][1, 77] = np.inf
+    c["x"][B - 1, 5], c["x"][B - 1, K - 3] = -np.inf, np.inf
+    y, ref = both()
+    others = [b for b in range(B) if b not in (1, B - 1)]
+    assert np.array_equal(y[others], clean[others])
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert (inf[1].any() or B == 2) and np.array_equal(y[inf], ref[inf])
+    fin = np.isfinite(ref)
+    assert np.abs(y[fin] - ref[fin]).max() <= 1e-5 * np.abs(clean).max()
+    c["x"][0], c["x"][1, 77] = np.nan, 1.0
+    y = layer(c) if not T else terms_layer(c)
+    assert np.isnan(y[0]).all()
+    assert np.array_equal(y[others[1:]], clean[others[1:]])
