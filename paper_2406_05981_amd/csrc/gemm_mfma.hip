@@ -334,12 +334,15 @@ __device__ __forceinline__ void split_body(const KernelArgs& ka, float* red) {
 #pragma unroll
                             for (int u = 0; u < SA_MAX_TERMS; ++u) {
                                 if (u >= a.terms) break;
-                                // sign 0: no term, whatever its exponent byte holds
+                                // sign 0: no term, whatever its exponent byte or the
+                                // activations hold (a select: 0 * inf is a NaN)
                                 const float sg = (float)(int8_t)(s[t][i][0] >> (8 * u));
                                 const float f = ldexpf(sg, (int)(int8_t)(e[t][i][0] >> (8 * u)));
 #pragma unroll
-                                for (int v = 0; v < 4; ++v)
-                                    sum[v] = i == 0 && u == 0 ? acc[v] * f : fmaf(acc[v], f, sum[v]);
+                                for (int v = 0; v < 4; ++v) {
+                                    const float z = i == 0 && u == 0 ? 0.0f : sum[v];
+                                    sum[v] = sg != 0.0f ? fmaf(acc[v], f, z) : z;
+                                }
                             }
                         } else {
                             const float f = ldexpf(1.0f, (int)(int8_t)e[t][i][0]);

@@ -1312,17 +1312,19 @@ __device__ __forceinline__ void gemm_batch_body(const BatchArgs& a, float* lut, 
                 asm volatile("" : "+v"(j.et[i]), "+v"(j.st[i]));
                 // the plane's signed terms (sign -1, 0 or +1: the products are
                 // exact), then the piece's weight once.  A sign of 0 means no
-                // term, whatever its exponent byte holds: its shift is replaced
-                // by 0 (a select, no branch), so 0 * ldexp(s, 127) = 0 * inf
-                // can never turn the sum into NaN.
+                // term, whatever its exponent byte or the activations hold (a
+                // select, no branch: 0 * inf would be a NaN).
                 float pl[kQuad] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int tt = 0; tt < kMaxTerms; ++tt) {
                     if (tt < a.terms) {
                         const float sg = (float)(int8_t)(j.st[i] >> (8 * tt));
-                        const int ex = sg != 0.0f ? (int)(int8_t)(j.et[i] >> (8 * tt)) : 0;
+                        const int ex = (int)(int8_t)(j.et[i] >> (8 * tt));
 #pragma unroll
-                        for (int u = 0; u < kQuad; ++u) pl[u] = fmaf(sg, ldexpf(s[u], ex), pl[u]);
+                        for (int u = 0; u < kQuad; ++u) {
+                            const float v = fmaf(sg, ldexpf(s[u], ex), pl[u]);
+                            pl[u] = sg != 0.0f ? v : pl[u];
+                        }
                     }
                 }
 #pragma unroll

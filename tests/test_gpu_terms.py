@@ -209,3 +209,27 @@ def test_sign_zero_terms_ignore_their_exponent(B, K):
     y = run(c)
     y_ref, a_ref = oracle.shiftadd_gemm_terms(c["x"], c["signs"], c["exps"], c["term_signs"], G)
     check(y, y_ref, a_ref, f"sign-0 terms, exponent 127, batch {B}")
+
+
+@pytest.mark.parametrize("q,N,K,B", [(2, 300, 4096, 1), (2, 300, 4096, 6), (2, 300, 1024, 6),
+                                     (2, 300, 1024, 13), (2, 4096, 4096, 16), (3, 300, 2048, 6),
+                                     (4, 4096, 512, 16)])
+def test_absent_terms_under_infinities(q, N, K, B):
+    """An infinite activation reaches an output by the terms that are there, on
+    every kernel (row, table and matrix-core)."""
+    say(f"absent terms under infinities q={q} N={N} K={K} B={B}")
+    T = 2
+    c = workloads.terms_case(q, N, K, 128, B, T, seed=59)
+    c["x"][0, 300] = np.inf
+    ts = c["term_signs"]
+    ts[:, :, 2, 1] = 0
+    ts[0, ::2, 2, :] = 0   # every second row: plane 0 has no term there
+    ts[:, 5, 2, :] = 0     # row 5: none at all
+    y = run(c)
+    with np.errstate(invalid="ignore"):
+        y_ref = oracle.shiftadd_gemm_terms(c["x"], c["signs"], c["exps"], ts, 128)[0]
+    assert np.isinf(y_ref[0]).sum() > N // 8 and np.isfinite(y_ref[0, 5])
+    assert np.array_equal(np.isnan(y), np.isnan(y_ref))
+    inf, fin = np.isinf(y_ref), np.isfinite(y_ref)
+    assert np.array_equal(y[inf], y_ref[inf])
+    assert np.abs(y[fin] - y_ref[fin]).max() <= 1e-5 * np.abs(y_ref[fin]).max()
