@@ -1234,8 +1234,9 @@ __device__ __forceinline__ void gemm_batch_body(const BatchArgs& a, float* lut, 
 
     float tot[kQuad] = {0.0f, 0.0f, 0.0f, 0.0f};
     auto query_job = [&](int pc, BatchJob<Q, KW>& j) {
-        // blocks past the end (last piece) repeat the last block: weight 0
-        const float keep = pieces * wave + pc < C16 ? 1.0f : 0.0f;
+        // blocks past the end (last piece) repeat the last block and are left out
+        // (a select: 0 * inf is a NaN)
+        const bool keep = pieces * wave + pc < C16;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             __builtin_amdgcn_sched_barrier(0);
@@ -1303,7 +1304,7 @@ __device__ __forceinline__ void gemm_batch_body(const BatchArgs& a, float* lut, 
             }
             if constexpr (BLK || COL) {
 #pragma unroll
-                for (int u = 0; u < kQuad; ++u) tot[u] += s[u] * keep;
+                for (int u = 0; u < kQuad; ++u) tot[u] += keep ? s[u] : 0.0f;
             } else if constexpr (ADD) {
                 if constexpr (PRE) {
                     j.et[i] = pre_field(pe[i], pc);
@@ -1328,10 +1329,10 @@ __device__ __forceinline__ void gemm_batch_body(const BatchArgs& a, float* lut, 
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < kQuad; ++u) tot[u] += pl[u] * keep;
+                for (int u = 0; u < kQuad; ++u) tot[u] += keep ? pl[u] : 0.0f;
             } else {
 #pragma unroll
-                for (int u = 0; u < kQuad; ++u) tot[u] += ldexpf(s[u], j.e[i]) * keep;
+                for (int u = 0; u < kQuad; ++u) tot[u] += keep ? ldexpf(s[u], j.e[i]) : 0.0f;
             }
         }
     };

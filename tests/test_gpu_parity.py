@@ -445,3 +445,42 @@ def test_small_then_large_row_counts():
     for c in (first, second, first, second):
         y_ref, a_ref = oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], 128)
         check(gemm(c), y_ref, a_ref, c["name"])
+
+
+@pytest.mark.parametrize("layout", ["row", "terms", "col", "blk"])
+@pytest.mark.parametrize("K,B", [(128, 2), (384, 13), (1280, 2), (4224, 13), (8320, 13), (1280, 1)])
+def test_infinity_in_the_last_block(layout, K, B):
+    """Waves without a block of their own repeat the last one and must leave it
+    out, infinities included."""
+    q, N = 2, 300
+    say(f"infinity in the last block: {layout} K={K} B={B}")
+    make = {"row": lambda: workloads.random_case(q, N, K, 128, B, seed=3, exp_range=(-10, -3)),
+            "terms": lambda: workloads.terms_case(q, N, K, 128, B, 2, seed=3),
+            "col": lambda: workloads.colwise_case(q, N, K, B, seed=3),
+            "blk": lambda: workloads.blockwise_case(q, N, K, B, 64, seed=3)}
+    c = make[layout]()
+    c["x"][0, K - 5] = np.inf
+    x, p = dev(c["x"]), pack(c["signs"])
+    y = torch.full((B, N), float("nan"), dtype=torch.float32, device="cuda")
+    with np.errstate(invalid="ignore"):
+        if layout == "row":
+            sa.sa_shiftadd_gemm(x, p, dev(c["exps"]), q, N, K, 128, B, y)
+            ref = oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], 128)[0]
+        elif layout == "terms":
+            sa.sa_shiftadd_gemm_terms(x, p, dev(c["exps"]), dev(c["term_signs"]), q, N, K, 128, 2,
+                                      B, y)
+            ref = oracle.shiftadd_gemm_terms(c["x"], c["signs"], c["exps"], c["term_signs"],
+                                             128)[0]
+        elif layout == "col":
+            sa.sa_shiftadd_gemm_colwise(x, p, dev(c["col_exps"]), q, N, K, B, y)
+            ref = oracle.shiftadd_gemm_colwise(c["x"], c["signs"], c["col_exps"])[0]
+        else:
+            sa.sa_shiftadd_gemm_blockwise(x, p, dev(c["blk_exps"]), q, N, K, 64, B, y)
+            ref = oracle.shiftadd_gemm_blockwise(c["x"], c["signs"], c["blk_exps"], 64)[0]
+    torch.cuda.synchronize()
+    y = y.cpu().numpy().astype(np.float64)
+    inf, fin = np.isinf(ref), np.isfinite(ref)
+    assert inf[0].sum() > N // 8
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(y[inf], ref[inf])
+    if fin.any():
+        assert np.abs(y[fin] - ref[fin]).max() <= 1e-5 * np.abs(ref[fin]).max()
