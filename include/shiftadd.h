@@ -208,9 +208,9 @@ SA_API int sa_quantize_bcq_terms(const float *w, int N, int K, int q, int group,
                                  void *stream);
 
 /* Launch geometry of the table kernels for a shape (host-only, no HIP call).
- * sa_shiftadd_gemm and sa_shiftadd_gemm_f16 run them at batch 1, for groups that
- * are not multiples of 128, for more than 4 planes and for small layers; other
- * calls run matrix-core kernels with a geometry of their own. */
+ * sa_shiftadd_gemm and sa_shiftadd_gemm_f16 run them wherever
+ * sa_plan_gemm_matrix reports kernel 0: at batch 1, for groups that are not
+ * multiples of 128, for more than 4 planes and for short layers. */
 typedef struct {
     int path;         /* 0: generic kernel (any group); group % 128 == 0: 1 row kernel
                          (batch 1), 2 batch kernel (batch >= 2); 3: the row kernel
@@ -227,6 +227,27 @@ typedef struct {
 } sa_plan;
 
 SA_API int sa_plan_gemm(int q, int N, int K, int group, int batch, sa_plan *plan);
+
+/* The matrix-core kernel a row-wise (terms = 0: sa_shiftadd_gemm,
+ * sa_shiftadd_gemm_f16) or additive (terms >= 1: sa_shiftadd_gemm_terms) call
+ * of this shape runs, and its geometry (host-only, no HIP call). */
+typedef struct {
+    int kernel;        /* 0: a table kernel with the geometry of sa_plan_gemm (the other
+                          fields are 0); 1: block-scaled fp4 x fp8 products (batch 2-8);
+                          2: binary16 products, a row's columns shared by waves; 3: binary16
+                          products, activations shared by waves */
+    int rows_per_wg;   /* output rows of a workgroup (the largest share) */
+    int batch_per_wg;  /* batch rows of a workgroup */
+    int workgroups;    /* workgroups of the launch */
+    int threads;       /* threads per workgroup */
+    int row_tiles;     /* 16-row tiles of a wave (kernels 1, 2) or a workgroup (3) */
+    int col_tiles;     /* matrix tiles of batch rows of a wave */
+    int column_shares; /* waves that share the input dimension */
+    size_t lds_bytes;  /* on-chip memory per workgroup */
+} sa_matrix_plan;
+
+SA_API int sa_plan_gemm_matrix(int q, int N, int K, int group, int terms, int batch,
+                               sa_matrix_plan *plan);
 
 /* The layer with column-wise scaling factors ("Ours (Acc.)", Sec. 4.2): one
  * power-of-two factor per plane and weight column (Eq. 2, one term, sign

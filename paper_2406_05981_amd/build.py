@@ -18,6 +18,8 @@ ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", name)
            for name in ("shiftadd.hip", "gemm_mx.hip", "gemm_mfma.hip", "bcq.hip", "alloc.hip")]
 INCLUDE = os.path.join(ROOT, "include")
+HEADERS = [os.path.join(INCLUDE, "shiftadd.h"), os.path.join(HERE, "csrc", "gemm_matrix.h"),
+           os.path.join(HERE, "csrc", "keys.h")]
 LIB = os.path.join(HERE, "libshiftadd.so")
 ARCH = "gfx950"
 

@@ -26,12 +26,13 @@
 // where its four MFMAs alone take 31; in the tile kernel (4 column tiles) the
 // expansion is shared and it is bound by the MFMAs and the LDS reads between
 // them, about 40% of the MFMA rate a register-only loop reaches.
-#include "gemm_mfma.h"
-
-#include "shiftadd.h"
+#include "gemm_matrix.h"
+#include "keys.h"
 
 namespace sa_mfma {
 namespace {
+
+using sa_matrix::Args;
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
@@ -44,31 +45,14 @@ constexpr int kTileThreads = 64 * kTileWaves;
 constexpr int kTile = 16;          // rows and batch rows of one MFMA tile
 constexpr int kGroupBlocks = 4;    // 128-column blocks per group: one 16-byte key load per lane
 
-__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
-
 struct KernelArgs {
     Args a;
     int row_wgs, col_wgs;  // grid
     int ksplit;            // split kernel: waves that share the columns (power of two)
     int NG;                // exponent groups of a row
-    uint32_t group_magic;  // block J is in group (J * magic) >> 32; 0: one block per group
+    uint32_t group_magic;  // sa_matrix::group_magic
     int vec;               // the exponents of 4 consecutive blocks load as one word (or two)
 };
-
-// Stored byte p of a row's 16 keys holds chunk (p + row) mod 16.  Returns the
-// keys in chunk order: out byte c = in byte (c - r) mod 16.
-__device__ inline void unrotate(const uint4 v, int r, uint32_t out[4]) {
-    const int s = (16 - r) & 15;
-    const uint32_t in[4] = {v.x, v.y, v.z, v.w};
-    uint32_t t[4], u[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-        t[d] = __builtin_amdgcn_alignbyte(in[(d + 1) & 3], in[d], (uint32_t)(s & 3));
-#pragma unroll
-    for (int d = 0; d < 4; ++d) u[d] = (s & 4) ? t[(d + 1) & 3] : t[d];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) out[d] = (s & 8) ? u[(d + 2) & 3] : u[d];
-}
 
 // Word b of the result holds byte b of the four words.
 __device__ inline void transpose_bytes(uint32_t w[4]) {
@@ -178,10 +162,7 @@ __device__ __forceinline__ void split_body(const KernelArgs& ka, float* red) {
     const Args& a = ka.a;
     constexpr int kE = ADD ? 4 : 1;
     const int C = a.K >> 3, C16 = C >> 4, NG = ka.NG;
-    // 128-column block -> exponent group
-    auto group_of = [&](int J) {
-        return ka.group_magic ? (int)__umulhi((uint32_t)J, ka.group_magic) : J;
-    };
+    auto group_of = [&](int J) { return sa_matrix::group_of(J, ka.group_magic); };
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
@@ -211,7 +192,6 @@ __device__ __forceinline__ void split_body(const KernelArgs& ka, float* red) {
         key_step[t] = 16 * imin(64, a.N - 64 * T);
         key_off[t] = (uint32_t)(64 * T * C + 16 * (n[t] & 63));
     }
-    const int rot = r;  // rows of a tile start at a multiple of 16: row mod 16 = r
     const uint16_t* xrow = a.x + (int64_t)imin(b0 + r, a.B - 1) * a.K + 8 * g;
 
     auto load_group = [&](int jg, Group<Q, RT, ADD>& k) {
@@ -292,7 +272,7 @@ __device__ __forceinline__ void split_body(const KernelArgs& ka, float* red) {
             for (int t = 0; t < RT; ++t)
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-                    unrotate(k.w[t][i], rot, kw[t][i]);
+                    rotate16(k.w[t][i], 16 - r, kw[t][i]);
                     transpose_bytes(kw[t][i]);
                     transpose4(kw[t][i]);
 #pragma unroll
@@ -453,8 +433,7 @@ __device__ __forceinline__ void tile_body(const KernelArgs& ka, uint4* xbuf) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     const int J = imin(J0 + b, C16 - 1);
-                    const int eg = ka.group_magic ? (int)__umulhi((uint32_t)J, ka.group_magic) : J;
-                    e |= (uint32_t)p[eg] << (8 * b);
+                    e |= (uint32_t)p[sa_matrix::group_of(J, ka.group_magic)] << (8 * b);
                 }
                 k.e[i] = e;
             }
@@ -517,7 +496,7 @@ __device__ __forceinline__ void tile_body(const KernelArgs& ka, uint4* xbuf) {
             if ((s & 3) == 0) {
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-                    unrotate(k.w[i], r, w[i]);
+                    rotate16(k.w[i], 16 - r, w[i]);
                     transpose_bytes(w[i]);
                     transpose4(w[i]);
                     e[i] = k.e[i];
@@ -612,60 +591,12 @@ __global__ __launch_bounds__(kTileThreads, Q <= 3 ? 3 : 2) void k_gemm_tile(Kern
 
 // ---------------------------------------------------------------- choice and launch
 
-struct Geometry {
-    int kind;  // 0: table kernel, 1: split, 2: tile
-    int rt, ct, rw, ksplit, sets;
-    double us;
-};
-
 // Rounds of workgroups over the 256 CUs; a partial round counts half as a whole
 // one, since several workgroups of a CU overlap.
 double rounds(int64_t wgs) {
     const double r = (double)wgs / 256;
     if (r <= 1) return 1;
     return 0.5 * (r + (double)((wgs + 255) / 256));
-}
-
-// The kernel and tiles with the least estimated time.  The estimates are fitted
-// to times measured over N 300..28672, K 640..11008, q 2..4, batch 9..256 (us,
-// within about 25%): the split kernel takes 1.05 per plane and row tile for each
-// 512-column group of a wave and round; the tile kernel 0.39 / 0.57 / 0.93 for
-// 1 / 2 / 4 column tiles per block and round (3 planes, four row tiles), at
-// least 0.80 / 0.95 / 1.27 when a CU has a single workgroup; the table kernel's
-// work grows with N K q batch (13.3 at 4096x4096 q=3 batch 16), and it walks the
-// columns in pieces of 1024 of about 1.05 each.  Short layers
-// are where the table kernel wins: 2000x1024 q=3 batch 16 4.0 against 6.4,
-// 768x768 3.8 against 6.8; 2000x2048 5.6 against 6.5.
-Geometry geometry(int q, int N, int K, int B, bool add) {
-    Geometry best{};
-    const double work = 10.8 * ((double)N * K * q * B) / (4096.0 * 4096 * 3 * 16);
-    const double walk = 1.05 * K / 1024 * 0.25 * (q + 1);
-    best.us = 0.95 * (2.5 + (work > walk ? work : walk));
-    const int blocks = K / 128, groups = (blocks + kGroupBlocks - 1) / kGroupBlocks;
-    int ksplit = 1;
-    while (ksplit < kWaves && ksplit < groups) ksplit *= 2;
-    const int sets = kWaves / ksplit, per_wave = (groups + ksplit - 1) / ksplit;
-    for (int rt = 1; rt <= (add ? 2 : 4); ++rt) {
-        const int64_t rows = (int64_t)kTile * rt * sets;
-        const double us = 2.5 + rounds((N + rows - 1) / rows * ((B + kTile - 1) / kTile)) *
-                                    (1.3 + per_wave * (1.05 * q * rt + 0.4));
-        if (us < best.us) best = {1, rt, 1, 0, ksplit, sets, us};
-    }
-    if (add) return best;
-    static const double kThrough[2][3] = {{0.39, 0.57, 0.93}, {0.55, 0.78, 1.27}};
-    static const double kAlone[2][3] = {{0.80, 0.95, 1.27}, {1.0, 1.2, 1.75}};
-    for (int ri = 0; ri < 2; ++ri)
-        for (int ci = 0; ci < 3; ++ci) {
-            const int rw = ri ? 2 : 4, ct = 1 << ci;
-            if (ct > 1 && B <= 8 * ct) continue;
-            const int64_t wgs = (int64_t)((N + kTile * rw - 1) / (kTile * rw)) *
-                                ((B + kTile * ct - 1) / (kTile * ct));
-            const double t = rounds(wgs) * kThrough[ri][ci];
-            const double us = 2.5 + (double)((blocks * rw + 3) / 4) * 0.25 * (q + 1) *
-                                        (t > kAlone[ri][ci] ? t : kAlone[ri][ci]);
-            if (us < best.us) best = {2, 1, ct, rw, 0, 0, us};
-        }
-    return best;
 }
 
 template <int RT, bool ADD>
@@ -692,50 +623,106 @@ void launch_tile(const KernelArgs& ka, int grid, hipStream_t s) {
 
 }  // namespace
 
-// Up to 4 planes (registers).  The index bounds: exact division by
-// multiplication (K), 32-bit key offsets (a plane holds fewer than 2^31 bytes).
-bool takes(int q, int N, int K, int G, int B, bool additive) {
-    if (q > 4 || B < 2 || K % 128 || G % 128 || K > (1 << 22)) return false;
-    return geometry(q, N, K, B, additive).kind != 0;
+// The kernel and tiles with the least estimated time.  The estimates are fitted
+// to times measured over N 300..28672, K 640..11008, q 2..4, batch 9..256 (us,
+// within about 25%): the split kernel takes 1.05 per plane and row tile for each
+// 512-column group of a wave and round; the tile kernel 0.39 / 0.57 / 0.93 for
+// 1 / 2 / 4 column tiles per block and round (3 planes, four row tiles), at
+// least 0.80 / 0.95 / 1.27 when a CU has a single workgroup; the table kernel's
+// work grows with N K q batch (13.3 at 4096x4096 q=3 batch 16), and it walks the
+// columns in pieces of 1024 of about 1.05 each.  Short layers
+// are where the table kernel wins: 2000x1024 q=3 batch 16 4.0 against 6.4,
+// 768x768 3.8 against 6.8; 2000x2048 5.6 against 6.5.
+// Up to 4 planes (registers).  The index bounds: exact division by multiplication
+// (K), 32-bit key offsets (a plane holds fewer than 2^31 bytes).
+double plan(int q, int N, int K, int G, int B, int terms, sa_matrix_plan* p) {
+    *p = sa_matrix_plan{};
+    (void)G;
+    if (K > (1 << 22)) return sa_matrix::kNever;
+    const bool add = terms > 0;
+    auto set = [&](int kernel, int row_tiles, int col_tiles, int shares, int rows, int threads,
+                   size_t lds) {
+        p->kernel = kernel;
+        p->row_tiles = row_tiles;
+        p->col_tiles = col_tiles;
+        p->column_shares = shares;
+        p->rows_per_wg = rows;
+        p->batch_per_wg = kTile * col_tiles;
+        p->workgroups = 8 * ((B + kTile * col_tiles - 1) / (kTile * col_tiles)) *
+                        (((N + rows - 1) / rows + 7) / 8);
+        p->threads = threads;
+        p->lds_bytes = lds;
+    };
+    const double work = 10.8 * ((double)N * K * q * B) / (4096.0 * 4096 * 3 * 16);
+    const double walk = 1.05 * K / 1024 * 0.25 * (q + 1);
+    double best = 0.95 * (2.5 + (work > walk ? work : walk));
+    const int blocks = K / 128, groups = (blocks + kGroupBlocks - 1) / kGroupBlocks;
+    int ksplit = 1;
+    while (ksplit < kWaves && ksplit < groups) ksplit *= 2;
+    const int sets = kWaves / ksplit, per_wave = (groups + ksplit - 1) / ksplit;
+    for (int rt = 1; rt <= (add ? 2 : 4); ++rt) {
+        const int64_t rows = (int64_t)kTile * rt * sets;
+        const double us = 2.5 + rounds((N + rows - 1) / rows * ((B + kTile - 1) / kTile)) *
+                                    (1.3 + per_wave * (1.05 * q * rt + 0.4));
+        if (us < best) {
+            best = us;
+            set(2, rt, 1, ksplit, (int)rows, kThreads, sizeof(float) * kWaves * rt * 256);
+        }
+    }
+    if (add) return p->kernel ? best : sa_matrix::kNever;
+    static const double kThrough[2][3] = {{0.39, 0.57, 0.93}, {0.55, 0.78, 1.27}};
+    static const double kAlone[2][3] = {{0.80, 0.95, 1.27}, {1.0, 1.2, 1.75}};
+    for (int ri = 0; ri < 2; ++ri)
+        for (int ci = 0; ci < 3; ++ci) {
+            const int rw = ri ? 2 : 4, ct = 1 << ci;
+            if (ct > 1 && B <= 8 * ct) continue;
+            const int64_t wgs = (int64_t)((N + kTile * rw - 1) / (kTile * rw)) *
+                                ((B + kTile * ct - 1) / (kTile * ct));
+            const double t = rounds(wgs) * kThrough[ri][ci];
+            const double us = 2.5 + (double)((blocks * rw + 3) / 4) * 0.25 * (q + 1) *
+                                        (t > kAlone[ri][ci] ? t : kAlone[ri][ci]);
+            if (us < best) {
+                best = us;
+                set(3, rw, ct, kTileWaves / rw, kTile * rw, kTileThreads,
+                    sizeof(uint4) * (kTileWaves / rw) * 2 * ct * 256);
+            }
+        }
+    return p->kernel ? best : sa_matrix::kNever;
 }
 
-void launch(const Args& a, hipStream_t s) {
+void launch(const Args& a, const sa_matrix_plan& p, hipStream_t s) {
     const bool add = a.terms > 0;
-    const Geometry g = geometry(a.q, a.N, a.K, a.B, add);
     KernelArgs ka{};
     ka.a = a;
-    const int64_t rows = kTile * (g.kind == 1 ? (int64_t)g.rt * g.sets : (int64_t)g.rw);
-    ka.row_wgs = (int)((a.N + rows - 1) / rows);
-    ka.col_wgs = (a.B + kTile * g.ct - 1) / (kTile * g.ct);
-    ka.ksplit = g.ksplit;
+    ka.row_wgs = (a.N + p.rows_per_wg - 1) / p.rows_per_wg;
+    ka.col_wgs = (a.B + p.batch_per_wg - 1) / p.batch_per_wg;
+    ka.ksplit = p.column_shares;
     ka.NG = a.K / a.G;
-    // J * magic >> 32 = J / d exactly while J * d < 2^32 (takes() bounds K)
-    const uint32_t d = (uint32_t)(a.G / 128);
-    ka.group_magic = d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
-    const uintptr_t p = reinterpret_cast<uintptr_t>(a.exps) |
+    ka.group_magic = sa_matrix::group_magic(a.G);
+    const uintptr_t e = reinterpret_cast<uintptr_t>(a.exps) |
                         (add ? reinterpret_cast<uintptr_t>(a.term_signs) : 0);
-    ka.vec = d == 1 && a.K % 512 == 0 && (p & (add ? 7u : 3u)) == 0 && (!add || a.terms == 2);
-    const int grid = 8 * ka.col_wgs * ((ka.row_wgs + 7) / 8);
-    if (g.kind == 2) {
-        if (g.rw == 4) {
-            if (g.ct == 1) launch_tile<1, 4>(ka, grid, s);
-            else if (g.ct == 2) launch_tile<2, 4>(ka, grid, s);
+    ka.vec = a.G == 128 && a.K % 512 == 0 && (e & (add ? 7u : 3u)) == 0 && (!add || a.terms == 2);
+    const int grid = p.workgroups;
+    if (p.kernel == 3) {
+        if (p.row_tiles == 4) {
+            if (p.col_tiles == 1) launch_tile<1, 4>(ka, grid, s);
+            else if (p.col_tiles == 2) launch_tile<2, 4>(ka, grid, s);
             else launch_tile<4, 4>(ka, grid, s);
         } else {
-            if (g.ct == 1) launch_tile<1, 2>(ka, grid, s);
-            else if (g.ct == 2) launch_tile<2, 2>(ka, grid, s);
+            if (p.col_tiles == 1) launch_tile<1, 2>(ka, grid, s);
+            else if (p.col_tiles == 2) launch_tile<2, 2>(ka, grid, s);
             else launch_tile<4, 2>(ka, grid, s);
         }
         return;
     }
     if (add) {
-        if (g.rt == 1) launch_split<1, true>(ka, grid, s);
+        if (p.row_tiles == 1) launch_split<1, true>(ka, grid, s);
         else launch_split<2, true>(ka, grid, s);
-    } else if (g.rt == 1) {
+    } else if (p.row_tiles == 1) {
         launch_split<1, false>(ka, grid, s);
-    } else if (g.rt == 2) {
+    } else if (p.row_tiles == 2) {
         launch_split<2, false>(ka, grid, s);
-    } else if (g.rt == 3) {
+    } else if (p.row_tiles == 3) {
         launch_split<3, false>(ka, grid, s);
     } else {
         launch_split<4, false>(ka, grid, s);

@@ -34,14 +34,15 @@
 // MB): 4096x4096 q=3 batch 2 8.1 -> 5.1, batch 4 8.2 -> 5.7, batch 8 9.2 -> 7.8;
 // 11008x4096 batch 4 12.5 -> 8.1; 28672x8192 batch 2 40.4 -> 22.0, batch 4
 // 40.8 -> 23.2, batch 8 73.4 -> 30.2; 8192x28672 batch 8 76.2 -> 41.8.
-#include "gemm_mx.h"
-
 #include <type_traits>
 
-#include "shiftadd.h"
+#include "gemm_matrix.h"
+#include "keys.h"
 
 namespace sa_mx {
 namespace {
+
+using sa_matrix::Args;
 
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef int int8v_t __attribute__((ext_vector_type(8)));
@@ -64,8 +65,6 @@ constexpr int kMaxTiles = 8;      // row tiles of one wave
 constexpr uint32_t kTopByte = 228;
 constexpr int kTopShift = 64;
 
-__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
-
 struct KernelArgs {
     Args a;
     int tiles;             // 16-row tiles, spread over (workgroup, row set)
@@ -73,21 +72,8 @@ struct KernelArgs {
     int ksplit;            // waves that share the columns (power of two <= kWaves)
     int sets;              // row sets of a workgroup: it has ksplit * sets waves
     int NG;                // exponent groups of a row
-    uint32_t group_magic;  // block J is in group (J * magic) >> 32; 0: one block per group
+    uint32_t group_magic;  // sa_matrix::group_magic
 };
-
-__device__ inline void unrotate(const uint4 v, int r, uint32_t out[4]) {
-    const int s = (16 - r) & 15;
-    const uint32_t in[4] = {v.x, v.y, v.z, v.w};
-    uint32_t t[4], u[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-        t[d] = __builtin_amdgcn_alignbyte(in[(d + 1) & 3], in[d], (uint32_t)(s & 3));
-#pragma unroll
-    for (int d = 0; d < 4; ++d) u[d] = (s & 4) ? t[(d + 1) & 3] : t[d];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) out[d] = (s & 8) ? u[(d + 2) & 3] : u[d];
-}
 
 // 32 signs as fp4 (e2m1) +-1.0: register v, nibble n holds bit 4n + v of the
 // word.  A set bit is +1.0 (0010), a clear one -1.0 (1010); the masks of a
@@ -99,15 +85,6 @@ __device__ inline int8v_t expand(uint32_t w, uint32_t and_mask = kAnd, uint32_t 
 #pragma unroll
     for (int v = 0; v < 4; ++v) a[v] = (int)(((w << (3 - v)) & and_mask) ^ xor_mask);
     return a;
-}
-
-// T consecutive bytes (exponents or signs of a group's terms), one per byte of
-// the result; 2 and 4 are aligned to their size (checked on the host).
-__device__ inline uint32_t load_terms(const uint8_t* p, int T) {
-    if (T == 4) return *reinterpret_cast<const uint32_t*>(p);
-    if (T == 2) return *reinterpret_cast<const uint16_t*>(p);
-    if (T == 3) return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16);
-    return p[0];
 }
 
 // Activations that are not finite stay out of the matrix core: what they add to an
@@ -230,16 +207,15 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
     auto load_keys = [&](int jg, int t, Keys<Q>& k) {
         const int n = imin(kTile * (tile0 + t) + r, a.N - 1);
         const int J = imin(kGroupBlocks * jg + g, C16 - 1);
-        const int eg = ka.group_magic ? (int)__umulhi((uint32_t)J, ka.group_magic) : J;
-        const uint32_t eoff = (uint32_t)(n * NG + eg);
+        const uint32_t eoff = (uint32_t)(n * NG + sa_matrix::group_of(J, ka.group_magic));
         const int T = n >> 6, R = imin(64, a.N - 64 * T);
         const uint32_t off = (uint32_t)(64 * T * C + 16 * (n & 63) + 16 * J * R);
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             if constexpr (ADD) {
                 const size_t o = ((size_t)i * a.N * NG + eoff) * a.terms;
-                k.e[i] = load_terms(reinterpret_cast<const uint8_t*>(a.exps) + o, a.terms);
-                k.s[i] = load_terms(reinterpret_cast<const uint8_t*>(a.term_signs) + o, a.terms);
+                k.e[i] = load_terms(a.exps + o, a.terms);
+                k.s[i] = load_terms(a.term_signs + o, a.terms);
             } else {
                 k.e[i] = (reinterpret_cast<const uint8_t*>(a.exps) + (size_t)i * a.N * NG)[eoff];
             }
@@ -399,7 +375,7 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                 uint32_t w[Q][4], e[Q], sg[Q];
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-                    unrotate(k.w[i], r, w[i]);
+                    rotate16(k.w[i], 16 - r, w[i]);
                     if constexpr (ADD) {
                         e[i] = k.e[i] ^ 0x80808080u;
                         sg[i] = k.s[i];
@@ -539,42 +515,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_mx(KernelArgs a) {
     body<Q, CT, NP, ADD>(a, reinterpret_cast<char*>(lds));
 }
 
-struct Geometry {
-    int ct, np, ksplit, sets, tiles, wgs;
-};
-
-Geometry geometry(int q, int N, int K, int B, int target = 0) {
-    Geometry g{};
-    (void)q;
-    const int groups = (K / 128 + kGroupBlocks - 1) / kGroupBlocks;
-    g.ksplit = 1;
-    while (g.ksplit < kWaves && g.ksplit < groups) g.ksplit *= 2;
-    g.ct = (B + 3) / 4;
-    g.np = B <= 2 ? 1 : B <= 4 ? 2 : 4;
-    g.tiles = (N + kTile - 1) / kTile;
-    const int resident = target ? target : 256;
-    g.sets = 1;
-    while (g.sets * g.ksplit < kWaves && g.tiles > resident * g.sets) g.sets *= 2;
-    const int sets = g.sets;
-    int w = (g.tiles + sets - 1) / sets;
-    if (w > resident) w = resident;
-    if ((g.tiles + w * sets - 1) / (w * sets) > kMaxTiles)
-        w = (g.tiles + kMaxTiles * sets - 1) / (kMaxTiles * sets);
-    g.wgs = w;
-    return g;
-}
-
-void set_args(KernelArgs& ka, const Geometry& g) {
-    const uint32_t d = (uint32_t)(ka.a.G / 128);
-    ka.tiles = g.tiles;
-    ka.shares = g.wgs * g.sets;
-    ka.sets = g.sets;
-    ka.ksplit = g.ksplit;
-    ka.NG = ka.a.K / ka.a.G;
-    // J * magic >> 32 = J / d exactly while J * d < 2^32 (takes() bounds K)
-    ka.group_magic = d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
-}
-
 template <int CT, int NP, bool ADD>
 void launch_q(const KernelArgs& ka, int grid, hipStream_t s) {
     const dim3 g(grid), b(64 * ka.ksplit * ka.sets);
@@ -587,10 +527,10 @@ void launch_q(const KernelArgs& ka, int grid, hipStream_t s) {
 }
 
 template <bool ADD>
-void launch_geometry(const KernelArgs& ka, const Geometry& g, hipStream_t s) {
-    if (g.np == 1) launch_q<1, 1, ADD>(ka, g.wgs, s);
-    else if (g.np == 2) launch_q<1, 2, ADD>(ka, g.wgs, s);
-    else launch_q<2, 4, ADD>(ka, g.wgs, s);
+void launch_batch(const KernelArgs& ka, int grid, hipStream_t s) {
+    if (ka.a.B <= 2) launch_q<1, 1, ADD>(ka, grid, s);
+    else if (ka.a.B <= 4) launch_q<1, 2, ADD>(ka, grid, s);
+    else launch_q<2, 4, ADD>(ka, grid, s);
 }
 
 }  // namespace
@@ -604,20 +544,47 @@ void launch_geometry(const KernelArgs& ka, const Geometry& g, hipStream_t s) {
 // 12000x1024 7.9 against 7.9, 300x4096 (4 planes) 7.6 against 8.7.
 // The index bounds: 32-bit offsets into a plane's exponents, exact division by
 // multiplication (K).
-bool takes(int q, int N, int K, int G, int B) {
-    if (q > 4 || B < 2 || B > 8 || K % 128 || G % 128 || K > (1 << 22)) return false;
-    if ((int64_t)N * (K / 128) >= (int64_t)1 << 31) return false;
-    if (B <= 4) return K >= 1536 || N >= 12000;
-    return K >= 4096 || (int64_t)N * K >= (int64_t)4096 * 2048;
+double plan(int q, int N, int K, int G, int B, int terms, sa_matrix_plan* p) {
+    *p = sa_matrix_plan{};
+    (void)G, (void)terms;
+    if (B > 8 || K > (1 << 22) || (int64_t)N * (K / 128) >= (int64_t)1 << 31)
+        return sa_matrix::kNever;
+    if (B <= 4 ? K < 1536 && N < 12000 : K < 4096 && (int64_t)N * K < (int64_t)4096 * 2048)
+        return sa_matrix::kNever;
+    const int groups = (K / 128 + kGroupBlocks - 1) / kGroupBlocks;
+    int ksplit = 1;
+    while (ksplit < kWaves && ksplit < groups) ksplit *= 2;
+    const int tiles = (N + kTile - 1) / kTile;
+    int sets = 1;
+    while (sets * ksplit < kWaves && tiles > 256 * sets) sets *= 2;
+    int wgs = imin((tiles + sets - 1) / sets, 256);
+    if ((tiles + wgs * sets - 1) / (wgs * sets) > kMaxTiles)
+        wgs = (tiles + kMaxTiles * sets - 1) / (kMaxTiles * sets);
+    const int share = (tiles + wgs * sets - 1) / (wgs * sets);
+    const int ct = B <= 4 ? 1 : 2;
+    p->kernel = 1;
+    p->rows_per_wg = kTile * sets * share;
+    p->batch_per_wg = B;
+    p->workgroups = wgs;
+    p->threads = 64 * ksplit * sets;
+    p->row_tiles = share;
+    p->col_tiles = ct;
+    p->column_shares = ksplit;
+    p->lds_bytes = (size_t)(ct == 1 ? lds_bytes<1>() : lds_bytes<2>());
+    return 0;  // wherever it is taken
 }
 
-void launch(const Args& a, hipStream_t s) {
+void launch(const Args& a, const sa_matrix_plan& p, hipStream_t s) {
     KernelArgs ka{};
     ka.a = a;
-    const Geometry g = geometry(a.q, a.N, a.K, a.B);
-    set_args(ka, g);
-    if (a.terms) launch_geometry<true>(ka, g, s);
-    else launch_geometry<false>(ka, g, s);
+    ka.ksplit = p.column_shares;
+    ka.sets = p.threads / (64 * ka.ksplit);
+    ka.tiles = (a.N + kTile - 1) / kTile;
+    ka.shares = p.workgroups * ka.sets;
+    ka.NG = a.K / a.G;
+    ka.group_magic = sa_matrix::group_magic(a.G);
+    if (a.terms) launch_batch<true>(ka, p.workgroups, s);
+    else launch_batch<false>(ka, p.workgroups, s);
 }
 
 }  // namespace sa_mx

@@ -10,9 +10,8 @@
 
 #include <stdint.h>
 
-
-#include "gemm_mfma.h"
-#include "gemm_mx.h"
+#include "gemm_matrix.h"
+#include "keys.h"
 #include "shiftadd.h"
 
 #define SA_VERSION_STRING "0.1.0 gfx950"
@@ -23,8 +22,6 @@ constexpr int kThreads = 256;     // 4 waves of 64
 constexpr int kTileRows = 64;     // rows per tile: one row per lane
 constexpr int kBlockChunks = 16;  // chunks (8 columns each) per block: 128 columns
 constexpr int kKeyStride = 64;    // floats per key in the LDS tables (256 bytes)
-
-__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
 
 // Byte offset of the key of (plane i, row n, chunk c) in the packed layout.
 // Rows come in tiles of 64 and chunks in blocks of 16; a 64-row tile of one
@@ -337,14 +334,6 @@ __device__ inline void load_job_keys(const RowsArgs& a, int n, int J, int C, int
 
 // Additive: the T exponents and term signs of the lane's group in every plane,
 // T consecutive bytes each (one load of 1, 2 or 4 bytes; three bytes for T = 3).
-__device__ inline uint32_t load_terms(const int8_t* p, int T) {
-    const uint8_t* b = reinterpret_cast<const uint8_t*>(p);
-    if (T == 4) return *reinterpret_cast<const uint32_t*>(b);
-    if (T == 2) return *reinterpret_cast<const uint16_t*>(b);
-    if (T == 3) return (uint32_t)b[0] | ((uint32_t)b[1] << 8) | ((uint32_t)b[2] << 16);
-    return b[0];
-}
-
 template <int Q>
 __device__ inline void load_job_terms(const RowsArgs& a, int n, int J, int NG, int bpg,
                                       JobRegs<Q>& j) {
@@ -367,21 +356,6 @@ __device__ inline void load_job_blk_exps(const RowsArgs& a, int n, int J, int C,
     for (int i = 0; i < Q; ++i)
         j.eb[i] = *reinterpret_cast<const uint4*>(a.blk_exps +
                                                   ((size_t)i * a.NB + rb) * C + 16 * J);
-}
-
-// Bytes of v rotated so that byte p of the result is byte (p + r) mod 16 of v:
-// the key at position p of a row is chunk (p + r) mod 16 of the block (r = row
-// mod 16), so the rotated exponents line up with the keys.
-__device__ inline void rotate16(const uint4 v, int r, uint32_t out[4]) {
-    const uint32_t in[4] = {v.x, v.y, v.z, v.w};
-    const uint32_t b = (uint32_t)(r & 3);
-    uint32_t t[4], u[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) t[d] = __builtin_amdgcn_alignbyte(in[(d + 1) & 3], in[d], b);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) u[d] = (r & 4) ? t[(d + 1) & 3] : t[d];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) out[d] = (r & 8) ? u[(d + 2) & 3] : u[d];
 }
 
 // Empty asm that "may modify" one plane's job registers: their consumers
@@ -1573,6 +1547,16 @@ void make_plan_blockwise(int q, int N, int K, int row_block, int batch, sa_plan*
     p->path = batch >= 2 ? 5 : 4;
 }
 
+// The matrix-core kernel of a row-wise (terms = 0) or additive batch and its
+// geometry; kernel 0: the table kernels of make_plan.
+void make_matrix_plan(int q, int N, int K, int group, int terms, int batch, sa_matrix_plan* p) {
+    *p = sa_matrix_plan{};
+    if (batch < 2 || q > 4 || group % 128) return;
+    if (sa_mx::plan(q, N, K, group, batch, terms, p) < sa_matrix::kNever) return;
+    if (sa_mfma::plan(q, N, K, group, batch, terms, p) < sa_matrix::kNever) return;
+    *p = sa_matrix_plan{};
+}
+
 int launch_status() { return hipGetLastError() == hipSuccess ? SA_OK : SA_ERR_HIP; }
 
 int grid_for(int64_t items) {
@@ -1718,18 +1702,29 @@ SA_API int sa_plan_gemm(int q, int N, int K, int group, int batch, sa_plan* plan
     return SA_OK;
 }
 
+SA_API int sa_plan_gemm_matrix(int q, int N, int K, int group, int terms, int batch,
+                               sa_matrix_plan* plan) {
+    if (!plan) return SA_ERR_NULL;
+    const int st = check_dims(q, N, K);
+    if (st != SA_OK) return st;
+    if (batch < 1 || batch > SA_MAX_BATCH || terms < 0 || terms > SA_MAX_TERMS) return SA_ERR_SHAPE;
+    if (group < 8 || (group & 7) || (K % group) || (terms && group % 128)) return SA_ERR_GROUP;
+    make_matrix_plan(q, N, K, group, terms, batch, plan);
+    return SA_OK;
+}
+
 // The layer with fp32 (out_half = 0) or binary16 (out_half = 1) outputs.
 int shiftadd_gemm(const uint16_t* x, const uint8_t* packed_bits, const int8_t* exps, int q, int N,
                   int K, int group, int batch, float* y, int out_half, void* stream) {
     const int st = validate_gemm(x, packed_bits, exps, q, N, K, group, batch, y);
     if (st != SA_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (sa_mx::takes(q, N, K, group, batch)) {
-        sa_mx::launch({x, packed_bits, exps, nullptr, q, N, K, group, batch, 0, y, out_half}, s);
-        return launch_status();
-    }
-    if (sa_mfma::takes(q, N, K, group, batch, false)) {
-        sa_mfma::launch({x, packed_bits, exps, nullptr, q, N, K, group, batch, 0, y, out_half}, s);
+    sa_matrix_plan mp;
+    make_matrix_plan(q, N, K, group, 0, batch, &mp);
+    if (mp.kernel) {
+        const sa_matrix::Args a = {x, packed_bits, exps, nullptr, q, N, K, group, batch, 0, y, out_half};
+        if (mp.kernel == 1) sa_mx::launch(a, mp, s);
+        else sa_mfma::launch(a, mp, s);
         return launch_status();
     }
     sa_plan plan;
@@ -1939,12 +1934,12 @@ SA_API int sa_shiftadd_gemm_terms(const uint16_t* x, const uint8_t* packed_bits,
     if ((reinterpret_cast<uintptr_t>(exps) & al) || (reinterpret_cast<uintptr_t>(term_signs) & al))
         return SA_ERR_ALIGN;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (sa_mx::takes(q, N, K, group, batch)) {
-        sa_mx::launch({x, packed_bits, exps, term_signs, q, N, K, group, batch, terms, y, 0}, s);
-        return launch_status();
-    }
-    if (sa_mfma::takes(q, N, K, group, batch, true)) {
-        sa_mfma::launch({x, packed_bits, exps, term_signs, q, N, K, group, batch, terms, y, 0}, s);
+    sa_matrix_plan mp;
+    make_matrix_plan(q, N, K, group, terms, batch, &mp);
+    if (mp.kernel) {
+        const sa_matrix::Args a = {x, packed_bits, exps, term_signs, q, N, K, group, batch, terms, y, 0};
+        if (mp.kernel == 1) sa_mx::launch(a, mp, s);
+        else sa_mfma::launch(a, mp, s);
         return launch_status();
     }
     sa_plan plan;

@@ -36,6 +36,12 @@ class SaPlan(ctypes.Structure):
     ]
 
 
+class SaMatrixPlan(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int) for name in (
+        "kernel", "rows_per_wg", "batch_per_wg", "workgroups", "threads", "row_tiles",
+        "col_tiles", "column_shares")] + [("lds_bytes", ctypes.c_size_t)]
+
+
 def _bind(lib):
     P = ctypes.c_void_p
     I = ctypes.c_int
@@ -48,6 +54,7 @@ def _bind(lib):
         "sa_shiftadd_gemm": ([P, P, P, I, I, I, I, I, P, P], I),
         "sa_shiftadd_gemm_f16": ([P, P, P, I, I, I, I, I, P, P], I),
         "sa_plan_gemm": ([I, I, I, I, I, ctypes.POINTER(SaPlan)], I),
+        "sa_plan_gemm_matrix": ([I, I, I, I, I, I, ctypes.POINTER(SaMatrixPlan)], I),
         "sa_kslice_workspace_bytes": ([I, I], ctypes.c_size_t),
         "sa_shiftadd_gemm_kslice": ([P, P, P, I, I, I, I, P, P, ctypes.c_size_t, P], I),
         "sa_shiftadd_gemm_colwise": ([P, P, P, I, I, I, I, P, P], I),
@@ -148,6 +155,13 @@ def sa_plan_gemm(q: int, N: int, K: int, group: int, batch: int) -> dict:
     p = SaPlan()
     _check(lib.sa_plan_gemm(q, N, K, group, batch, ctypes.byref(p)), "sa_plan_gemm")
     return {name: getattr(p, name) for name, _ in SaPlan._fields_}
+
+
+def sa_plan_gemm_matrix(q: int, N: int, K: int, group: int, batch: int, terms: int = 0) -> dict:
+    p = SaMatrixPlan()
+    _check(lib.sa_plan_gemm_matrix(q, N, K, group, terms, batch, ctypes.byref(p)),
+           "sa_plan_gemm_matrix")
+    return {name: getattr(p, name) for name, _ in SaMatrixPlan._fields_}
 
 
 def sa_plan_gemm_colwise(q: int, N: int, K: int, batch: int) -> dict:

@@ -318,3 +318,37 @@ def test_alloc_validation_codes():
     w2 = L.sa_importance_workspace()
     assert L.sa_importance_criterion(A, 4, 64, A, A, A, w2 - 8, None) == sa.SA_ERR_SHAPE
     assert L.sa_importance_criterion(A, 0, 64, A, A, A, w2, None) == sa.SA_ERR_SHAPE
+
+
+def test_matrix_plan_validation_codes():
+    p = sa.SaMatrixPlan()
+    ref = ctypes.byref(p)
+    f = sa.lib.sa_plan_gemm_matrix
+    assert f(3, 4096, 4096, 128, 0, 8, None) == sa.SA_ERR_NULL
+    assert f(9, 4096, 4096, 128, 0, 8, ref) == sa.SA_ERR_Q
+    assert f(3, 0, 4096, 128, 0, 8, ref) == sa.SA_ERR_SHAPE
+    assert f(3, 4096, 4096, 128, 0, 0, ref) == sa.SA_ERR_SHAPE
+    assert f(3, 4096, 4096, 128, 0, sa.SA_MAX_BATCH + 1, ref) == sa.SA_ERR_SHAPE
+    assert f(3, 4096, 4096, 128, -1, 8, ref) == sa.SA_ERR_SHAPE
+    assert f(3, 4096, 4096, 128, sa.SA_MAX_TERMS + 1, 8, ref) == sa.SA_ERR_SHAPE
+    assert f(3, 4096, 4096, 24, 0, 8, ref) == sa.SA_ERR_GROUP
+    assert f(3, 4096, 4096, 64, 2, 8, ref) == sa.SA_ERR_GROUP   # as the additive entry point
+
+
+def test_matrix_plan_tells_the_kernel_of_a_call():
+    """Batch 1, more than 4 planes and groups below 128 run table kernels; the
+    grids cover every output and the workgroups fit a compute unit."""
+    for q, N, K, G, B in [(3, 4096, 4096, 128, 1), (5, 4096, 4096, 128, 16),
+                          (3, 4096, 4096, 64, 16), (3, 768, 768, 128, 8)]:
+        assert set(sa.sa_plan_gemm_matrix(q, N, K, G, B).values()) == {0}
+    kernels = set()
+    for q, N, K, G, B, T in [(3, 4096, 4096, 128, 2, 0), (3, 8192, 28672, 128, 8, 0),
+                             (3, 4096, 4096, 128, 16, 0), (2, 4096, 11008, 128, 16, 2),
+                             (3, 11003, 4096, 128, 250, 0)]:
+        p = sa.sa_plan_gemm_matrix(q, N, K, G, B, T)
+        kernels.add(p["kernel"])
+        rows = -(-N // p["rows_per_wg"])
+        assert p["workgroups"] >= rows * -(-B // p["batch_per_wg"])
+        assert p["threads"] <= 512 and 0 < p["lds_bytes"] <= 160 * 1024
+        assert p["batch_per_wg"] in (B, 16 * p["col_tiles"])
+    assert kernels == {1, 2, 3}

@@ -77,7 +77,7 @@ def test_library_host_code_under_sanitizers():
     sys.path.insert(0, ROOT)
     from paper_2406_05981_amd import build as hip_build
 
-    srcs = hip_build.SOURCES + [os.path.join(ROOT, "include", "shiftadd.h")]
+    srcs = hip_build.SOURCES + hip_build.HEADERS
     os.makedirs(CACHE, exist_ok=True)
     lib = os.path.join(CACHE, f"libshiftadd_san_{_digest(srcs)}.so")
     if not os.path.exists(lib):
