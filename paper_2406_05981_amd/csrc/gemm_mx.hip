@@ -392,17 +392,26 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                 else if (more)
                     load_keys(jg + ka.ksplit, 0, k);
                 __builtin_amdgcn_sched_barrier(0);
-                float4_t acc[CT][2];
+                // Every 32 columns' products are 4 roundings of fp32 behind the largest,
+                // so the chains are kept short: row-wise one accumulator a step, over
+                // the planes; additive two, whose first piece (the others are 2^-5 of
+                // it) is taken out after every term.
+                constexpr int NA = ADD ? 2 : 4;
+                float4_t acc[CT][NA];
+                float first[CT];
                 auto step = [&](auto mc, const int8v_t W, uint32_t es) {
                     constexpr int m = decltype(mc)::value;
 #pragma unroll
                     for (int c = 0; c < CT; ++c)
-                        acc[c][m & 1] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                            X[c][m], W, acc[c][m & 1], 0, 4, m, (int)xs[c], 0, (int)es);
+                        acc[c][m % NA] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                            X[c][m], W, acc[c][m % NA], 0, 4, m, (int)xs[c], 0, (int)es);
                 };
 #pragma unroll
-                for (int c = 0; c < CT; ++c)
-                    acc[c][0] = acc[c][1] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int c = 0; c < CT; ++c) {
+                    first[c] = 0.0f;
+#pragma unroll
+                    for (int d = 0; d < NA; ++d) acc[c][d] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                }
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
                     if constexpr (ADD) {
@@ -419,6 +428,11 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                             step(std::integral_constant<int, 3>{}, expand(w[i][3], am, xm8), es);
                             e[i] >>= 8;
                             sg[i] >>= 8;
+#pragma unroll
+                            for (int c = 0; c < CT; ++c) {
+                                first[c] += acc[c][0][0] + acc[c][1][0];
+                                acc[c][0][0] = acc[c][1][0] = 0.0f;
+                            }
                         }
                     } else {
                         step(std::integral_constant<int, 0>{}, expand(w[i][0]), e[i]);
@@ -430,8 +444,9 @@ __device__ __forceinline__ void body(const KernelArgs& ka, char* lds) {
                 // a lane's results are the pieces of one (row, batch row)
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    const float4_t s = acc[c][0] + acc[c][1];
-                    float v = ((s[3] + s[2]) + s[1]) + s[0];
+                    float4_t s = acc[c][0] + acc[c][1];
+                    if constexpr (!ADD) s += acc[c][2] + acc[c][3];
+                    float v = ((s[3] + s[2]) + s[1]) + (s[0] + first[c]);
                     if (pass) v = ldexpf(v, kTopShift + 1);
 #pragma unroll
                     for (int u = 0; u < kMaxTiles; ++u)

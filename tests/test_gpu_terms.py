@@ -144,7 +144,7 @@ def test_one_term_batch_matches_row_wise_batch_kernel():
 def test_one_term_batch_matches_row_wise_batch_kernel_preloaded():
     """K = 4096: the additive kernel preloads its exponents and term signs,
     the row-wise kernel loads them per piece; still the same arithmetic."""
-    q, N, K, G, B = 3, 1024, 4096, 128, 8
+    q, N, K, G, B = 3, 300, 4096, 128, 13
     c = workloads.terms_case(q, N, K, G, B, 1, seed=13)
     assert (c["term_signs"] != 0).all()
     y = run(c)
