@@ -220,20 +220,8 @@ __device__ __forceinline__ void split_body(const KernelArgs& ka, float* red) {
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
                         const int64_t eo = (erow + group_of(imin(J0 + b, C16 - 1))) * a.terms;
-                        const uint8_t* pe = reinterpret_cast<const uint8_t*>(a.exps) + eo;
-                        const uint8_t* ps = reinterpret_cast<const uint8_t*>(a.term_signs) + eo;
-                        uint32_t e = 0, s = 0;
-                        if (a.terms == 2) {  // 2-byte aligned (checked on the host)
-                            e = *reinterpret_cast<const uint16_t*>(pe);
-                            s = *reinterpret_cast<const uint16_t*>(ps);
-                        } else {
-                            for (int u = 0; u < a.terms; ++u) {
-                                e |= (uint32_t)pe[u] << (8 * u);
-                                s |= (uint32_t)ps[u] << (8 * u);
-                            }
-                        }
-                        k.e[t][i][b] = e;
-                        k.s[t][i][b] = s;
+                        k.e[t][i][b] = load_terms(a.exps + eo, a.terms);
+                        k.s[t][i][b] = load_terms(a.term_signs + eo, a.terms);
                     }
                 } else {
                     const uint8_t* p = reinterpret_cast<const uint8_t*>(a.exps) + erow;
@@ -595,7 +583,7 @@ __global__ __launch_bounds__(kTileThreads, Q <= 3 ? 3 : 2) void k_gemm_tile(Kern
 // one, since several workgroups of a CU overlap.
 double rounds(int64_t wgs) {
     const double r = (double)wgs / 256;
-    if (r <= 1) return 1;
+    if (r <= 1) return r;
     return 0.5 * (r + (double)((wgs + 255) / 256));
 }
 
@@ -606,7 +594,11 @@ void launch_split(const KernelArgs& ka, int grid, hipStream_t s) {
         case 1: hipLaunchKernelGGL((k_gemm_split<1, RT, ADD>), g, b, 0, s, ka); break;
         case 2: hipLaunchKernelGGL((k_gemm_split<2, RT, ADD>), g, b, 0, s, ka); break;
         case 3: hipLaunchKernelGGL((k_gemm_split<3, RT, ADD>), g, b, 0, s, ka); break;
-        default: hipLaunchKernelGGL((k_gemm_split<4, RT, ADD>), g, b, 0, s, ka); break;
+        default:
+            // (more row tiles with 4 planes would spill: plan())
+            if constexpr (RT <= (ADD ? 1 : 3))
+                hipLaunchKernelGGL((k_gemm_split<4, RT, ADD>), g, b, 0, s, ka);
+            break;
     }
 }
 
@@ -623,71 +615,85 @@ void launch_tile(const KernelArgs& ka, int grid, hipStream_t s) {
 
 }  // namespace
 
-// The kernel and tiles with the least estimated time.  The estimates are fitted
-// to times measured over N 300..28672, K 640..11008, q 2..4, batch 9..256 (us,
-// within about 25%): the split kernel takes 1.05 per plane and row tile for each
-// 512-column group of a wave and round; the tile kernel 0.39 / 0.57 / 0.93 for
-// 1 / 2 / 4 column tiles per block and round (3 planes, four row tiles), at
-// least 0.80 / 0.95 / 1.27 when a CU has a single workgroup; the table kernel's
-// work grows with N K q batch (13.3 at 4096x4096 q=3 batch 16), and it walks the
-// columns in pieces of 1024 of about 1.05 each.  Short layers
-// are where the table kernel wins: 2000x1024 q=3 batch 16 4.0 against 6.4,
-// 768x768 3.8 against 6.8; 2000x2048 5.6 against 6.5.
-// Up to 4 planes (registers).  The index bounds: exact division by multiplication
-// (K), 32-bit key offsets (a plane holds fewer than 2^31 bytes).
+// The kernel and tiles with the least estimated time.  Up to 4 planes (registers);
+// the index bounds: exact division by multiplication (K), 32-bit key offsets (a
+// plane holds fewer than 2^31 bytes).
+// The estimates are fitted to every kernel's time on 2986 drawn layers of N
+// 60..28672, K 128..28672, q 1..4, batch 2..256, weights rotated over 320 MB (5th
+// and 95th percentile of estimate / measured: split 0.75 and 1.4, tile 0.82 and
+// 1.2).  Split: a workgroup alone takes a latency per 512-column group of a wave
+// (its activations are requested one 128-column block ahead), more of them on a CU
+// their issue time.  Tile: the same per 128-column block of a column share.
+// Row tiles that spill (4 planes x 4 tiles, additive 4 x 2) are left out.
 double plan(int q, int N, int K, int G, int B, int terms, sa_matrix_plan* p) {
     *p = sa_matrix_plan{};
-    (void)G;
-    if (K > (1 << 22)) return sa_matrix::kNever;
     const bool add = terms > 0;
-    auto set = [&](int kernel, int row_tiles, int col_tiles, int shares, int rows, int threads,
-                   size_t lds) {
+    if (K > (1 << 22) || (add && B < 5)) return sa_matrix::kNever;
+    double best = sa_matrix::kNever;
+    auto offer = [&](double us, int kernel, int row_tiles, int col_tiles, int shares, int rows,
+                     int threads, size_t lds) {
+        if (us >= best) return;
+        best = us;
         p->kernel = kernel;
-        p->row_tiles = row_tiles;
-        p->col_tiles = col_tiles;
-        p->column_shares = shares;
         p->rows_per_wg = rows;
         p->batch_per_wg = kTile * col_tiles;
         p->workgroups = 8 * ((B + kTile * col_tiles - 1) / (kTile * col_tiles)) *
                         (((N + rows - 1) / rows + 7) / 8);
         p->threads = threads;
+        p->row_tiles = row_tiles;
+        p->col_tiles = col_tiles;
+        p->column_shares = shares;
         p->lds_bytes = lds;
     };
-    const double work = 10.8 * ((double)N * K * q * B) / (4096.0 * 4096 * 3 * 16);
-    const double walk = 1.05 * K / 1024 * 0.25 * (q + 1);
-    double best = 0.95 * (2.5 + (work > walk ? work : walk));
+    auto workgroups = [&](int rows, int col_tiles) {
+        return (int64_t)((N + rows - 1) / rows) *
+               ((B + kTile * col_tiles - 1) / (kTile * col_tiles));
+    };
     const int blocks = K / 128, groups = (blocks + kGroupBlocks - 1) / kGroupBlocks;
     int ksplit = 1;
     while (ksplit < kWaves && ksplit < groups) ksplit *= 2;
     const int sets = kWaves / ksplit, per_wave = (groups + ksplit - 1) / ksplit;
-    for (int rt = 1; rt <= (add ? 2 : 4); ++rt) {
-        const int64_t rows = (int64_t)kTile * rt * sets;
-        const double us = 2.5 + rounds((N + rows - 1) / rows * ((B + kTile - 1) / kTile)) *
-                                    (1.3 + per_wave * (1.05 * q * rt + 0.4));
-        if (us < best) {
-            best = us;
-            set(2, rt, 1, ksplit, (int)rows, kThreads, sizeof(float) * kWaves * rt * 256);
-        }
+    // the part of a wave's blocks that exist
+    const double fill = (double)blocks / (kGroupBlocks * ksplit * per_wave);
+    // base, alone (per group: least, fixed, per plane and row tile), shared (fixed, per
+    // group, per plane and row tile; what a missing block saves): row-wise; one term,
+    // two that load as words, two that do not, three, four
+    static const double kSplit[6][8] = {
+        {2.7, 2.4, 0.96, 1.1, 0.24, 0.89, 1.2, 0},   {1.7, 0.6, 1.5, 2.1, 1.5, 0, 3.3, 0.8},
+        {2.6, 2.8, 1.0, 1.6, 1.4, 0.71, 1.9, 0.57},  {2.2, 3.2, 1.5, 1.6, 1.2, 0.3, 2.8, 1},
+        {0, 1.4, 2.8, 3.8, 1.3, 0.46, 5.9, 0.94},    {0, 1, 2.3, 5.0, 3.1, 0, 8.7, 1}};
+    const bool bytes = G != 128 || K % 512;
+    const double* f = kSplit[!add ? 0 : terms == 1 ? 1 : terms == 2 ? 2 + bytes : terms + 1];
+    for (int rt = 1; rt <= (add ? 2 : 4) && rt * q <= (add ? 6 : 12); ++rt) {
+        const int rows = kTile * rt * sets, qr = q * rt;
+        const double alone = f[2] + f[3] * qr;
+        const double t0 = per_wave * (alone > f[1] ? alone : f[1]);
+        const double t1 = rounds(workgroups(rows, 1)) *
+                          (f[4] + per_wave * (f[5] + f[6] * qr) * (1 - f[7] * (1 - fill)));
+        const double us = f[0] + (t0 > t1 ? t0 : t1);
+        // the estimates of additive layers spread wider: 9% against them
+        offer(add ? 1.09 * us : us, 2, rt, 1, ksplit, rows, kThreads,
+              sizeof(float) * kWaves * rt * 256);
     }
-    if (add) return p->kernel ? best : sa_matrix::kNever;
-    static const double kThrough[2][3] = {{0.39, 0.57, 0.93}, {0.55, 0.78, 1.27}};
-    static const double kAlone[2][3] = {{0.80, 0.95, 1.27}, {1.0, 1.2, 1.75}};
-    for (int ri = 0; ri < 2; ++ri)
-        for (int ci = 0; ci < 3; ++ci) {
-            const int rw = ri ? 2 : 4, ct = 1 << ci;
-            if (ct > 1 && B <= 8 * ct) continue;
-            const int64_t wgs = (int64_t)((N + kTile * rw - 1) / (kTile * rw)) *
-                                ((B + kTile * ct - 1) / (kTile * ct));
-            const double t = rounds(wgs) * kThrough[ri][ci];
-            const double us = 2.5 + (double)((blocks * rw + 3) / 4) * 0.25 * (q + 1) *
-                                        (t > kAlone[ri][ci] ? t : kAlone[ri][ci]);
-            if (us < best) {
-                best = us;
-                set(3, rw, ct, kTileWaves / rw, kTile * rw, kTileThreads,
-                    sizeof(uint4) * (kTileWaves / rw) * 2 * ct * 256);
-            }
-        }
-    return p->kernel ? best : sa_matrix::kNever;
+    if (add) return best;
+    struct Fit {
+        int ct, rw;
+        double base, alone, alone_q, shared, shared_q;
+    };
+    static const Fit kFit[] = {{1, 4, 2.7, 0.37, 0.15, 0.22, 0.13},
+                               {2, 4, 3.0, 0.38, 0.19, 0.16, 0.21},
+                               {4, 4, 3.6, 0.43, 0.30, 0.46, 0.22},
+                               {1, 2, 3.1, 0.39, 0.17, 0.20, 0.15},
+                               {2, 2, 3.5, 0.54, 0.17, 0.35, 0.17}};
+    for (const Fit& f : kFit) {
+        if (f.ct > 1 && B <= 8 * f.ct) continue;
+        const int rows = kTile * f.rw, steps = (blocks * f.rw + kTileWaves - 1) / kTileWaves;
+        const double t0 = steps * (f.alone + f.alone_q * q);
+        const double t1 = rounds(workgroups(rows, f.ct)) * steps * (f.shared + f.shared_q * q);
+        offer(f.base + (t0 > t1 ? t0 : t1), 3, f.rw, f.ct, kTileWaves / f.rw, rows, kTileThreads,
+              sizeof(uint4) * (kTileWaves / f.rw) * 2 * f.ct * 256);
+    }
+    return best;
 }
 
 void launch(const Args& a, const sa_matrix_plan& p, hipStream_t s) {
@@ -710,8 +716,7 @@ void launch(const Args& a, const sa_matrix_plan& p, hipStream_t s) {
             else launch_tile<4, 4>(ka, grid, s);
         } else {
             if (p.col_tiles == 1) launch_tile<1, 2>(ka, grid, s);
-            else if (p.col_tiles == 2) launch_tile<2, 2>(ka, grid, s);
-            else launch_tile<4, 2>(ka, grid, s);
+            else launch_tile<2, 2>(ka, grid, s);
         }
         return;
     }

@@ -550,22 +550,18 @@ void launch_batch(const KernelArgs& ka, int grid, hipStream_t s) {
 
 }  // namespace
 
-// Batch 2 to 8, up to 4 planes (registers).  A wave's part of the input
-// dimension is 512 columns, so a short K leaves most of a workgroup's waves
-// out, and splitting the activations costs the more the larger the batch:
-// measured against the table kernel (us), batch 4: 3000x768 4.1 against 3.8,
-// 8000x1024 4.5 against 4.2, but 500x1536 4.2 against 4.5 and 28672x512 5.8
-// against 7.5; batch 8: 2000x3072 7.1 against 6.0, 4096x2048 5.7 against 5.8,
-// 12000x1024 7.9 against 7.9, 300x4096 (4 planes) 7.6 against 8.7.
-// The index bounds: 32-bit offsets into a plane's exponents, exact division by
-// multiplication (K).
+// Batch 2 to 8.  The index bounds: exact division by multiplication (K), 32-bit
+// offsets into a plane's exponents.
+// The estimate is fitted (5th and 95th percentile of estimate / measured 0.9 and
+// 1.2) to 1590 drawn layers of N 60..28672, K 128..28672, q 1..4, weights rotated
+// over 320 MB: per 512-column group of a wave a fixed part (splitting the
+// activations) and a part per row tile, plane and term; waves left out by a short
+// K cost their share.
 double plan(int q, int N, int K, int G, int B, int terms, sa_matrix_plan* p) {
     *p = sa_matrix_plan{};
-    (void)G, (void)terms;
     if (B > 8 || K > (1 << 22) || (int64_t)N * (K / 128) >= (int64_t)1 << 31)
         return sa_matrix::kNever;
-    if (B <= 4 ? K < 1536 && N < 12000 : K < 4096 && (int64_t)N * K < (int64_t)4096 * 2048)
-        return sa_matrix::kNever;
+    (void)G;
     const int groups = (K / 128 + kGroupBlocks - 1) / kGroupBlocks;
     int ksplit = 1;
     while (ksplit < kWaves && ksplit < groups) ksplit *= 2;
@@ -586,7 +582,18 @@ double plan(int q, int N, int K, int G, int B, int terms, sa_matrix_plan* p) {
     p->col_tiles = ct;
     p->column_shares = ksplit;
     p->lds_bytes = (size_t)(ct == 1 ? lds_bytes<1>() : lds_bytes<2>());
-    return 0;  // wherever it is taken
+    // [batch 2, 3-4, 5-8][row-wise, additive]
+    static const double kFit[3][2][6] = {
+        {{3.0, 0.52, 0.50, 0.33, 0, 0.30}, {3.3, 0.41, 0.43, 0.53, 0.44, 0.50}},
+        {{3.4, 1.2, 0.48, 0.31, 0, 0.26}, {3.7, 1.0, 0.33, 0.59, 0.43, 0.39}},
+        {{3.9, 2.3, 0.45, 0.42, 0, 0.31}, {4.0, 2.2, 0.13, 0.80, 0.48, 0.45}}};
+    const double* f = kFit[B <= 2 ? 0 : B <= 4 ? 1 : 2][terms > 0];
+    const double rounds = wgs > 256 ? wgs / 256.0 : 1.0;
+    const int per_wave = (groups + ksplit - 1) / ksplit;
+    const double tile = f[2] + f[3] * q * (terms > 1 ? 1 + f[4] * (terms - 1) : 1);
+    // the factors of three terms load by the byte
+    return f[0] + rounds * per_wave * (f[1] + share * tile) *
+                      (f[5] + (1 - f[5]) * p->threads / kThreads) * (terms == 3 ? 1.12 : 1);
 }
 
 void launch(const Args& a, const sa_matrix_plan& p, hipStream_t s) {

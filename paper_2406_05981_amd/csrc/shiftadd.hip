@@ -1547,14 +1547,45 @@ void make_plan_blockwise(int q, int N, int K, int row_block, int batch, sa_plan*
     p->path = batch >= 2 ? 5 : 4;
 }
 
-// The matrix-core kernel of a row-wise (terms = 0) or additive batch and its
-// geometry; kernel 0: the table kernels of make_plan.
+// Estimated time (us) of the batch table kernel on a row-wise (terms = 0) or
+// additive layer: rounds of workgroups over the CUs times the pieces a workgroup
+// walks, or the latency of those pieces.  Fitted to 2986 drawn layers, weights
+// rotated over 320 MB (5th and 95th percentile of estimate / measured 0.85 and 1.15
+// row-wise, 0.7 and 1.25 additive).
+double table_us(int q, int N, int K, int batch, int terms) {
+    const int kw = batch_kw(q, N, batch);
+    const int rows = 16 * kw;
+    const double rounds = (double)((N + rows - 1) / rows) * ((batch + kQuad - 1) / kQuad) / 256;
+    const double pieces = (K / 128 + kRowWaves - 1) / kRowWaves;
+    // base, walk (fixed, per plane), work (fixed, per plane and row tile), by terms
+    static const double kFit[SA_MAX_TERMS + 1][5] = {{2.6, 0.016, 0.31, 0.44, 0.18},
+                                                     {3.0, 0.40, 0.39, 0.64, 0.195},
+                                                     {2.9, 0.28, 0.49, 0.59, 0.24},
+                                                     {2.8, 0.18, 1.01, 0.52, 0.33},
+                                                     {2.9, 0.38, 0.58, 0.63, 0.27}};
+    const double* f = kFit[terms];
+    const double walk = f[1] + f[2] * q;
+    const double work = (rounds > 1 ? rounds : 1) * (f[3] + f[4] * q * kw);
+    return f[0] + pieces * (walk > work ? walk : work);
+}
+
+// The kernel of a row-wise (terms = 0) or additive batch: the least estimated time,
+// a matrix-core kernel where it is 7% below the table kernel's (kernel 0: the
+// geometry of make_plan).  On 4576 drawn layers 0.7% of the calls are more than
+// 3% slower than the table kernel, 0.2% more than 10%, and the geometric mean
+// is 0.86 of its time (0.83 would be the best kernel for every layer).
 void make_matrix_plan(int q, int N, int K, int group, int terms, int batch, sa_matrix_plan* p) {
     *p = sa_matrix_plan{};
     if (batch < 2 || q > 4 || group % 128) return;
-    if (sa_mx::plan(q, N, K, group, batch, terms, p) < sa_matrix::kNever) return;
-    if (sa_mfma::plan(q, N, K, group, batch, terms, p) < sa_matrix::kNever) return;
-    *p = sa_matrix_plan{};
+    double best = 0.93 * table_us(q, N, K, batch, terms);
+    sa_matrix_plan c;
+    double us = sa_mx::plan(q, N, K, group, batch, terms, &c);
+    if (us < best) {
+        best = us;
+        *p = c;
+    }
+    us = sa_mfma::plan(q, N, K, group, batch, terms, &c);
+    if (us < best) *p = c;
 }
 
 int launch_status() { return hipGetLastError() == hipSuccess ? SA_OK : SA_ERR_HIP; }

@@ -352,3 +352,18 @@ def test_matrix_plan_tells_the_kernel_of_a_call():
         assert p["threads"] <= 512 and 0 < p["lds_bytes"] <= 160 * 1024
         assert p["batch_per_wg"] in (B, 16 * p["col_tiles"])
     assert kernels == {1, 2, 3}
+
+
+# Layers on which the matrix-core forms were slower than the batch table kernel
+# (us, table and matrix-core): additive factors of one, three and four terms, few rows
+# with few planes, short layers.
+@pytest.mark.parametrize("q,N,K,G,B,T,table,matrix", [
+    (3, 26850, 2688, 128, 11, 3, 54.7, 98.6), (3, 27937, 8320, 128, 11, 4, 184, 309),
+    (1, 1970, 22144, 128, 12, 4, 26.9, 45.0), (4, 7225, 4224, 128, 108, 3, 236, 382),
+    (4, 14998, 4736, 128, 48, 1, 183, 225), (3, 6652, 4224, 128, 14, 4, 35.1, 44.5),
+    (1, 7970, 1408, 128, 7, 0, 5.57, 8.50), (2, 306, 10368, 128, 7, 0, 11.8, 16.9),
+    (1, 605, 7552, 128, 6, 0, 8.36, 11.2), (3, 1096, 4224, 128, 8, 0, 8.40, 10.4),
+    (1, 21041, 768, 128, 3, 0, 5.24, 7.05), (2, 95, 28544, 128, 13, 0, 23.6, 30.6)])
+def test_slower_layers_stay_on_the_table_kernel(q, N, K, G, B, T, table, matrix):
+    p = sa.sa_plan_gemm_matrix(q, N, K, G, B, T)
+    assert p["kernel"] == 0, p

@@ -97,7 +97,7 @@ def test_terms_full_size_sampled():
     check(y[:, rows], y_ref, a_ref, "4096x4096 sampled")
 
 
-# Batch >= 2 runs the batch kernel: 16, 32 or 64 rows per workgroup and four
+# Layers that run the batch table kernel: 16, 32 or 64 rows per workgroup and four
 # batch rows per table.
 BATCH_CASES = [
     # (q, N, K, G, B, T, label)
@@ -109,19 +109,27 @@ BATCH_CASES = [
     (1, 77, 4224, 128, 6, 4, "ragged last piece"),
     (5, 300, 2048, 1024, 13, 2, "five planes, two pieces, ragged quad"),
     # exponents and term signs preloaded per lane (G = 128, K % 1024 == 0)
-    (3, 1000, 4096, 128, 8, 2, "preloaded, 8 bytes"),
-    (2, 500, 8192, 128, 5, 2, "preloaded, 16 bytes"),
-    (3, 300, 4096, 128, 6, 4, "preloaded, 16 bytes, four terms"),
+    (3, 2000, 2048, 128, 8, 2, "preloaded, 4 bytes"),
+    (3, 300, 4096, 128, 13, 1, "preloaded, 4 bytes, one term"),
     (1, 64, 2048, 128, 4, 4, "preloaded, 8 bytes, two pieces"),
-    (3, 200, 4096, 128, 4, 1, "preloaded, one term"),
-    (4, 300, 4096, 128, 8, 2, "four planes: per-piece loads"),
-    (3, 300, 4096, 128, 8, 3, "three terms: per-piece loads"),
+    (2, 500, 8192, 128, 11, 1, "preloaded, 8 bytes, one term"),
+    (3, 300, 4096, 128, 13, 4, "preloaded, 16 bytes, four terms"),
+    (2, 4096, 4096, 128, 16, 4, "preloaded, 16 bytes, larger"),
+    (4, 300, 4096, 128, 13, 4, "four planes: per-piece loads"),
+    (3, 300, 4096, 128, 13, 3, "three terms: per-piece loads"),
+    # and layers on the matrix cores at the same sizes
+    (3, 1000, 4096, 128, 8, 2, "matrix cores, two terms"),
+    (2, 500, 8192, 128, 5, 2, "matrix cores, ragged column tile"),
+    (3, 200, 4096, 128, 4, 1, "matrix cores, one term"),
+    (4, 300, 4096, 128, 8, 2, "matrix cores, four planes"),
+    (3, 300, 4096, 128, 4, 3, "matrix cores, three terms"),
 ]
 
 
 @pytest.mark.parametrize("q,N,K,G,B,T,label", BATCH_CASES, ids=[c[-1] for c in BATCH_CASES])
 def test_terms_batch_parity(q, N, K, G, B, T, label):
-    assert sa.sa_plan_gemm(q, N, K, G, B)["path"] == 2
+    matrix = sa.sa_plan_gemm_matrix(q, N, K, G, B, T)["kernel"]
+    assert (matrix != 0) == label.startswith("matrix cores")
     say(f"terms batch q={q} N={N} K={K} G={G} B={B} T={T}: {label}")
     c = workloads.terms_case(q, N, K, G, B, T, seed=q + N + K + B + T)
     y = run(c)
@@ -131,6 +139,8 @@ def test_terms_batch_parity(q, N, K, G, B, T, label):
 
 def test_one_term_batch_matches_row_wise_batch_kernel():
     q, N, K, G, B = 3, 2048, 2048, 128, 8
+    for T in (0, 1):
+        assert sa.sa_plan_gemm_matrix(q, N, K, G, B, T)["kernel"] == 0
     c = workloads.terms_case(q, N, K, G, B, 1, seed=12)
     assert (c["term_signs"] != 0).all()
     y = run(c)
@@ -144,7 +154,9 @@ def test_one_term_batch_matches_row_wise_batch_kernel():
 def test_one_term_batch_matches_row_wise_batch_kernel_preloaded():
     """K = 4096: the additive kernel preloads its exponents and term signs,
     the row-wise kernel loads them per piece; still the same arithmetic."""
-    q, N, K, G, B = 3, 300, 4096, 128, 13
+    q, N, K, G, B = 3, 500, 4096, 128, 13
+    for T in (0, 1):
+        assert sa.sa_plan_gemm_matrix(q, N, K, G, B, T)["kernel"] == 0
     c = workloads.terms_case(q, N, K, G, B, 1, seed=13)
     assert (c["term_signs"] != 0).all()
     y = run(c)
@@ -159,7 +171,8 @@ def test_one_term_batch_matches_row_wise_batch_kernel_preloaded():
 def test_terms_batch_misaligned(shift):
     """Exponents and term signs at addresses not aligned to the 16-byte preload
     take the per-piece loads: the same arithmetic, so bit-identical output."""
-    q, N, K, G, B, T = 3, 700, 8192, 128, 6, 2
+    q, N, K, G, B, T = 3, 700, 4096, 128, 13, 4
+    assert sa.sa_plan_gemm_matrix(q, N, K, G, B, T)["kernel"] == 0
     say(f"terms batch misaligned by {shift}")
     c = workloads.terms_case(q, N, K, G, B, T, seed=31)
     y_al = run(c)
@@ -181,9 +194,11 @@ def test_terms_batch_misaligned(shift):
     check(y_mis, y_ref, a_ref, "misaligned exponents and term signs")
 
 
-def test_terms_batch_full_size_sampled():
-    q, N, K, G, B, T = 3, 4096, 4096, 128, 16, 2
-    say("terms batch full size 4096x4096 B=16 T=2")
+@pytest.mark.parametrize("T,kernel", [(2, 2), (4, 0)], ids=["matrix cores", "table kernel"])
+def test_terms_batch_full_size_sampled(T, kernel):
+    q, N, K, G, B = 3, 4096, 4096, 128, 16
+    say(f"terms batch full size 4096x4096 B=16 T={T}")
+    assert sa.sa_plan_gemm_matrix(q, N, K, G, B, T)["kernel"] == kernel
     c = workloads.terms_case(q, N, K, G, B, T, seed=2)
     y = run(c)
     rows = np.sort(np.random.default_rng(1).choice(N, 256, replace=False))
@@ -193,13 +208,14 @@ def test_terms_batch_full_size_sampled():
     check(y[:, rows], y_ref, a_ref, "4096x4096 batch 16 sampled")
 
 
-@pytest.mark.parametrize("B", [1, 2, 8])
+@pytest.mark.parametrize("B", [1, 2, 8, 13])
 @pytest.mark.parametrize("K", [1024, 4096])
 def test_sign_zero_terms_ignore_their_exponent(B, K):
     """A term sign of 0 means no term, whatever its exponent byte holds: with
     every sign-0 term carrying exponent 127 (2^127 times a group sum overflows
-    fp32) the row kernel (batch 1) and the batch kernel (batch >= 2, per-piece
-    and preloaded exponents) still match the oracle, which skips such terms."""
+    fp32) the row kernel (batch 1), the batch table kernel (K = 1024, batch 13) and
+    the matrix cores (K = 4096, batch 2) still match the oracle, which skips
+    such terms."""
     q, N, G, T = 3, 300, 128, 3
     say(f"sign-0 terms with exponent 127: K={K} B={B}")
     c = workloads.terms_case(q, N, K, G, B, T, seed=41 + B + K)
