@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 
 METRIC = "µs/layer and achieved HBM GB/s (% of peak) for shift-add GEMV, batch 1–16"
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published peak
-KERNEL_SRC = os.path.join(ROOT, "paper_2406_05981_amd", "csrc", "shiftadd.hip")
+CSRC = os.path.join(ROOT, "paper_2406_05981_amd", "csrc")
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -46,9 +46,20 @@ def algorithmic_bytes(q: int, N: int, K: int, G: int, B: int) -> int:
     return q * N * K // 8 + q * N * (K // G) + 2 * B * K + 4 * B * N
 
 
-def source_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+# the source of each kernel: its file without comments, up to the host code that
+# chooses and launches it (neither changes what a launch moves)
+KERNEL_FILES = {"k_gemm_mx": "gemm_mx.hip", "k_gemm_split": "gemm_mfma.hip",
+                "k_gemm_tile": "gemm_mfma.hip"}
+
+
+def source_hash(kernel: str) -> str:
+    h = hashlib.sha256()
+    base = next((k for k in KERNEL_FILES if kernel.startswith(k)), "")
+    for name in ("keys.h", KERNEL_FILES.get(base, "shiftadd.hip")):
+        with open(os.path.join(CSRC, name)) as f:
+            code = re.split(r"^// -{40,} (?:choice and launch|host side)$", f.read(), flags=re.M)[0]
+            h.update(" ".join(re.sub(r"//.*", "", code).split()).encode())
+    return h.hexdigest()[:16]
 
 
 # the dominant kernel of each launch path; the additive layer ("add") runs the
@@ -56,6 +67,8 @@ def source_hash() -> str:
 KERNELS = {0: "k_gemm_generic", 1: "k_gemm_rows", 2: "k_gemm_batch", 3: "k_gemm_rows_col",
            4: "k_gemm_rows_blk", 5: "k_gemm_batch_blk", 6: "k_gemm_batch_col", "add1": "k_gemm_rows_add",
            "add2": "k_gemm_batch_add", "kslice": "k_gemm_kslice"}
+# ... and the matrix-core kernels of sa_plan_gemm_matrix
+MATRIX_KERNELS = {1: "k_gemm_mx", 2: "k_gemm_split", 3: "k_gemm_tile"}
 
 
 def measured_traffic(kernel: str, workload: str, layer: int, batch: int):
@@ -69,7 +82,7 @@ def measured_traffic(kernel: str, workload: str, layer: int, batch: int):
     if not m:
         return None
     rec = json.loads(m.group(1))
-    if rec.get("source_sha256_16") != source_hash():
+    if rec.get("source_sha256_16") != source_hash(kernel):
         return None
     return rec.get("bytes_per_launch")
 
@@ -720,6 +733,11 @@ def main() -> int:
             ranges = max(1, min(256 // slices, -(-(-(-N // 8)) // 16)))
             plan = {"path": "kslice", "rows_per_wg": -(-N // ranges), "workgroups": slices * ranges,
                     "threads": 1024, "pieces": 1, "lds_bytes": 131072}
+    matrix = None
+    if not (blockwise or colwise or args.kslice):
+        mp = sa.sa_plan_gemm_matrix(q, N, K, G, B, terms)
+        if mp["kernel"]:
+            matrix, plan = MATRIX_KERNELS[mp["kernel"]], mp
     copies = max(1, math.ceil(args.rotate_mb * 1e6 / weight_bytes))
     mode = (" column-wise" if colwise else " block-wise" if blockwise else
             f" additive, {terms} terms" if terms else " whole tables, K slices" if args.kslice
@@ -831,12 +849,7 @@ def main() -> int:
         read_floor = time_read_floor(sa, bytes_step, args.rotate_mb, args.steps, stream)
         log(f"read floor: {read_floor}")
 
-    kernel = KERNELS[plan["path"]]
-    # the plan describes the table kernels; the library picks a matrix-core kernel
-    # for most row-wise and additive batches of up to 4 planes
-    label = kernel
-    if plan["path"] in (2, "add2") and q <= 4:
-        label = f"matrix cores (k_gemm_mx, k_gemm_split, k_gemm_tile); short layers {kernel}"
+    kernel = matrix or KERNELS[plan["path"]]
     traffic = measured_traffic(kernel + (f"_t{terms}" if terms else ""), args.workload,
                                args.layer, B)
     out = {
@@ -859,14 +872,15 @@ def main() -> int:
             "N": N, "K": K, "q": q, "group": None if colwise or blockwise else G, "batch": B,
             "tables": ("256 entries per chunk, 1024-column K slices, partials added in slice "
                        "order by a second kernel" if args.kslice else
-                       "factored 16-entry halves per chunk"),
+                       "none: planes expanded in registers, products on the matrix cores"
+                       if matrix else "factored 16-entry halves per chunk"),
             "scales": ("column-wise (one exponent per plane and column)" if colwise else
                        f"block-wise (8 columns x {rb} rows)" if blockwise else
                        f"row-wise, group {G}, additive, {terms} terms" if terms else
                        f"row-wise, group {G}"),
             "weight_copies": copies,
             "launch": "eager" if args.eager else "hip graph replay",
-            "kernel": label,
+            "kernel": kernel,
             "rows_per_workgroup": plan["rows_per_wg"],
             "workgroups": plan["workgroups"],
         },

@@ -530,6 +530,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_mx(KernelArgs a) {
     body<Q, CT, NP, ADD>(a, reinterpret_cast<char*>(lds));
 }
 
+// ---------------------------------------------------------------- choice and launch
+
 template <int CT, int NP, bool ADD>
 void launch_q(const KernelArgs& ka, int grid, hipStream_t s) {
     const dim3 g(grid), b(64 * ka.ksplit * ka.sets);
