@@ -518,10 +518,14 @@ __device__ __forceinline__ void tile_body(const KernelArgs& ka, uint4* xbuf) {
                         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
                             X[m], cat(A[i][4 * m], A[i][4 * m + 1], A[i][4 * m + 2], A[i][4 * m + 3]),
                             m == 0 ? float4_t{0.0f, 0.0f, 0.0f, 0.0f} : acc[i], 0, 0, 0);
+                // a block's planes first: shorter chains of additions
 #pragma unroll
-                for (int i = 0; i < Q; ++i)
+                for (int v = 0; v < 4; ++v) {
+                    float sum = acc[0][v] * f[0];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) part[c][v] = fmaf(acc[i][v], f[i], part[c][v]);
+                    for (int i = 1; i < Q; ++i) sum = fmaf(acc[i][v], f[i], sum);
+                    part[c][v] += sum;
+                }
             }
             if ((s & 3) == 3 || J + 1 == blk1) {
 #pragma unroll

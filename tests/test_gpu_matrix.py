@@ -328,6 +328,22 @@ def test_massive_outliers(B, outlier):
     assert e <= 1.1 * er
 
 
+@pytest.mark.parametrize("q,N,K,B,kernel", [
+    (4, 8001, 512, 60, TILE), (3, 2000, 640, 255, TILE), (3, 5003, 4096, 250, TILE),
+    (3, 4096, 4096, 16, SPLIT), (1, 15556, 640, 9, SPLIT), (3, 4170, 4096, 8, MX)])
+def test_error_as_the_table_kernel(q, N, K, B, kernel):
+    """Ordinary activations with 1% of the channels x20: no further from 64 bits
+    than the fp32 tables (1.1: the two add in different orders)."""
+    say(f"error q={q} N={N} K={K} B={B}")
+    c = workloads.random_case(q, N, K, 128, B, seed=60, exp_range=(-10, -3),
+                              outlier_fraction=0.01)
+    runs(c, kernel)
+    ref = oracle.shiftadd_gemm(c["x"], c["signs"], c["exps"], 128)[0]
+    e, er = norm_error(layer(c), ref), norm_error(table_batch(c), ref)
+    say(f"  error {e:.3e}, table kernel {er:.3e}")
+    assert e <= 1.1 * er
+
+
 @pytest.mark.parametrize("q,N,B,T", [(4, 2300, 4, 4), (3, 4170, 8, 2), (3, 4170, 2, 2)])
 @pytest.mark.parametrize("outlier", [20.0, 1000.0, 30000.0])
 def test_massive_outliers_additive(q, N, B, T, outlier):
