@@ -140,6 +140,28 @@ def test_large_batch(shape, kernel, row_tiles, col_tiles, shares):
     check(layer(c), c, c["name"])
 
 
+# (q, N, K, G, B) that stay on the batch table kernel, its row-tile height: 32 and 64
+# rows over one, two and three pieces at 1 to 5 planes, a wide plane count, ragged
+# rows, eight batch quads
+KEPT = [
+    ((1, 4100, 128, 128, 2), 32), ((1, 5374, 1152, 128, 2), 32), ((2, 4952, 256, 256, 2), 32),
+    ((2, 4218, 2432, 128, 2), 32), ((3, 4100, 2304, 128, 3), 32), ((4, 2547, 256, 128, 6), 32),
+    ((1, 11297, 256, 128, 2), 64), ((2, 8977, 1152, 128, 3), 64), ((2, 4590, 2176, 128, 5), 64),
+    ((3, 8323, 1152, 384, 3), 64), ((4, 8603, 640, 128, 3), 64), ((7, 4099, 1152, 128, 9), 64),
+    ((5, 8201, 256, 128, 32), 64),
+]
+
+
+@pytest.mark.parametrize("shape,rows", KEPT)
+def test_table_kernel_kept(shape, rows):
+    q, N, K, G, B = shape
+    say(f"table form q={q} N={N} K={K} G={G} B={B}")
+    c = workloads.random_case(q, N, K, G, B, seed=43, exp_range=(-12, -3), outlier_fraction=0.01)
+    runs(c, 0)
+    assert sa.sa_plan_gemm(q, N, K, G, B)["rows_per_wg"] == rows
+    check(layer(c), c, c["name"])
+
+
 def terms_layer(c, shift=0):
     y = torch.full((c["B"], c["N"]), float("nan"), dtype=torch.float32, device="cuda")
     e, s = dev(c["exps"]).reshape(-1), dev(c["term_signs"]).reshape(-1)

@@ -154,17 +154,18 @@ SMALL = [
     # decoder projections sharing an input run as one launch: q+k at q=2
     # (8192x4096), up+gate at q=3 (22016x4096)
     (2, 8192, 4096, 128, 1), (3, 22016, 4096, 128, 1),
-    # batch kernel (group % 128 == 0, batch >= 2), 16- and 32-row workgroups
+    # batches of 2 and more (group % 128 == 0): most of these run the table kernel's
+    # 16-row workgroups over 1 to 8 pieces
     (2, 300, 384, 128, 2), (3, 257, 1280, 256, 3), (4, 130, 768, 768, 5),
     (2, 1000, 4096, 128, 16), (3, 63, 2048, 128, 4), (2, 129, 1152, 384, 7),
     (3, 4100, 384, 384, 13), (8, 40, 384, 128, 6), (6, 300, 2176, 128, 9),
-    # batch kernel, 64-row workgroups over three pieces
+    # ... three matrix-core forms (the table kernel's 32- and 64-row workgroups are
+    # in test_gpu_matrix.py)
     (3, 4096, 2304, 128, 16),
-    # batch kernel, 64-row workgroups (last piece and last tile ragged)
     (1, 28672, 1152, 128, 5), (2, 28000, 256, 256, 8),
-    # batch kernel, 64-row workgroups, eight quads
+    # ... eight batch quads
     (1, 28600, 256, 128, 32),
-    # batch kernel, every wave over 4, 8, 16 and 2 consecutive blocks
+    # ... 4, 8, 16 and 2 blocks a wave of the table kernel, or the block-scaled form
     (3, 1000, 4096, 128, 4), (2, 300, 8192, 128, 16), (4, 100, 16384, 128, 3),
     (1, 64, 2048, 128, 2),
     # generic kernel (any group % 8 == 0)
