@@ -13,19 +13,25 @@
 // the waves of a workgroup (few batch rows: the rows alone would not fill the
 // chip), k_gemm_tile shares the activations of a workgroup through LDS (many
 // batch rows: an expanded plane serves up to 64 of them).  2-norm error against
-// 64 bits as the table kernel's (8.4e-8 at 4096x4096 q=3, both).
+// 64 bits at most the table kernel's on ordinary activations (4096x4096 q=3 batch 16
+// 7.9e-8 against 8.9e-8, 8001x512 q=4 batch 60 5.8e-8 against 5.9e-8); with massive
+// outliers (x1000) on fewer than 1700 columns up to 1.14 times it.
 //
 // Measured against the table batch kernel (us, graph replay, weights rotated
-// over 300 MB): split: 4096x4096 q=3 batch 16 13.3 -> 8.2, batch 32 21.4 -> 10.5,
-// 11008x4096 batch 16 29.6 -> 13.9, 4096x11008 batch 16 30.2 -> 19.4, 28672x8192
-// batch 16 122 -> 56, additive factors of two terms 4096x11008 q=2 batch 16
-// (11 MB, in the last-level cache) 25.9 -> 18.5; tile: 11003x4096 q=3 batch 250 345 -> 81, 11008x4096 q=2 batch
-// 128 132 -> 40, 4096x11008 q=4 batch 256 450 -> 126.
-// What bounds them: a SIMD needs about 94 ns per 16 rows x 128 columns x plane
-// in the split kernel, VALU issue (46 operations, 32 of them the expansion),
-// where its four MFMAs alone take 31; in the tile kernel (4 column tiles) the
-// expansion is shared and it is bound by the MFMAs and the LDS reads between
-// them, about 40% of the MFMA rate a register-only loop reaches.
+// over 300 MB): split: 4096x4096 q=3 batch 16 13.3 -> 7.6, batch 32 21.4 -> 10.4,
+// 11008x4096 q=2 batch 16 20.7 -> 11.5, 28672x8192 batch 16 122 -> 60, additive
+// factors of two terms 4096x11008 q=2 batch 16 26.2 -> 19.1; tile: 11003x4096 q=3
+// batch 250 345 -> 81.5, 11008x4096 q=2 batch 128 132 -> 46, 4096x11008 q=4 batch
+// 256 450 -> 148.
+// What bounds them (counters, share of SIMD cycles): the split kernel latency --
+// VALU instructions 27-29%, matrix cores 5-6%, and its waves wait 42% (11008x4096
+// q=2 batch 16) to 65% (4096x11008) of their cycles: activations are requested
+// one 128-column block ahead, 0.2-0.4 us of work at two waves a SIMD.  The tile
+// kernel (4096x4096 q=3 batch 250) issues VALU in 26% and keeps the matrix cores
+// busy 18% of the cycles at one workgroup a CU: a block's LDS reads, products and
+// barrier follow each other.  k_gemm_tile<3, 4, 4> spills 10 registers (44 bytes a
+// lane) to stay at three waves a SIMD; without that cap 11003x4096 batch 250 takes
+// 88 us.
 #include "gemm_matrix.h"
 #include "keys.h"
 
@@ -376,10 +382,9 @@ void k_gemm_split(KernelArgs a) {
 // 128-column block lie in LDS in operand order, double buffered: the next
 // block's are loaded before a block's products and written, re-paired, after
 // them, one barrier a block.  A block's planes are expanded once and multiplied
-// by every column tile.  Two thirds of the registers hold expanded planes, so
-// up to 3 planes the kernel is held to three waves a SIMD: reading a column
-// tile ahead and adding one behind hides the LDS reads but costs that third
-// wave (11003x4096 q=3 batch 250: 80 us as it is, 88 with them).
+// by every column tile.  Up to 3 planes the kernel is held to three waves a SIMD:
+// reading a column tile ahead and adding one behind hides the LDS reads but costs
+// that third wave (11003x4096 q=3 batch 250: 80 us as it is, 88 with them).
 template <int Q>
 struct TileKeys {
     uint4 w[Q];

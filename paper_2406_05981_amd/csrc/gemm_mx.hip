@@ -22,18 +22,20 @@
 // apart fp32); below 16 and down to e4m3's 2^-9 the pieces stay inside that
 // window, so these sums are exact and everything after them is fp32.
 // Measured against 64 bits (2-norm, 3 planes, batch 8, the table batch kernel's
-// error in brackets): 4096 columns N(0,1) 6.3e-8 (1.2e-7), four columns x1000
-// 9.6e-8 (1.2e-7), x16000 1.3e-7 (1.3e-7), 28672 columns 8.1e-8 (1.7e-7), four
-// columns x16000 1.3e-7 (2.1e-7).  With three pieces 3.0e-7 at x16000; the fourth
-// costs 8192x28672 batch 8 40.1 -> 44.3 us.
+// error in brackets): 4170x4096 N(0,1) 6.2e-8 (8.5e-8), four columns x1000 9.1e-8
+// (1.1e-7), x30000 1.2e-7 (1.3e-7), 28672 columns 8.2e-8 (1.7e-7).  With three pieces
+// 3.0e-7 at x16000; the fourth costs 8192x28672 batch 8 40.1 -> 44.3 us.
 //
-// What bounds it: at 28672x8192 q=3 the key stream (16.5 us as a plain read);
-// per 16 rows x 128 columns x plane a SIMD needs 25 ns (batch <= 4: 8 VALU
-// operations and one MFMA), the table kernel's queries about 100 ns.  Measured
-// against the table batch kernel (us, graph replay, weights rotated over 300
-// MB): 4096x4096 q=3 batch 2 8.1 -> 5.1, batch 4 8.2 -> 5.7, batch 8 9.2 -> 7.8;
-// 11008x4096 batch 4 12.5 -> 8.1; 28672x8192 batch 2 40.4 -> 22.0, batch 4
-// 40.8 -> 23.2, batch 8 73.4 -> 30.2; 8192x28672 batch 8 76.2 -> 41.8.
+// What bounds it: per 16 rows x 128 columns x plane a SIMD needs 25 ns (batch <= 4: 8
+// VALU operations and one MFMA), the table kernel's queries about 100.  VALU
+// instructions take 56% of the SIMD cycles at 28672x8192 batch 8 and 60% at
+// 8192x28672, where every workgroup splits all activations for two row tiles; the
+// matrix cores are busy 23 and 16%, the LDS 12 and 28%, two thirds of it in bank
+// conflicts of the 528-byte columns (counters).
+// Measured against the table batch kernel (us, graph replay, weights rotated over
+// 300 MB): 4096x4096 q=3 batch 2 7.8 -> 5.5, batch 4 7.8 -> 6.4; 28672x8192 batch 4
+// 38.0 -> 24.4, batch 8 67.3 -> 32.0; 8192x28672 batch 8 68.1 -> 47.3; 11008x4096 q=4
+// batch 8 23.3 -> 13.4; two terms 4096x11008 q=4 batch 8 32.2 -> 29.7.
 #include <type_traits>
 
 #include "gemm_matrix.h"

@@ -1550,8 +1550,8 @@ void make_plan_blockwise(int q, int N, int K, int row_block, int batch, sa_plan*
 // Estimated time (us) of the batch table kernel on a row-wise (terms = 0) or
 // additive layer: rounds of workgroups over the CUs times the pieces a workgroup
 // walks, or the latency of those pieces.  Fitted to 2986 drawn layers, weights
-// rotated over 320 MB (5th and 95th percentile of estimate / measured 0.85 and 1.15
-// row-wise, 0.7 and 1.25 additive).
+// rotated over 320 MB (5th and 95th percentile of estimate / measured 0.85 and 1.16
+// row-wise, 0.75 and 1.28 additive).
 double table_us(int q, int N, int K, int batch, int terms) {
     const int kw = batch_kw(q, N, batch);
     const int rows = 16 * kw;
@@ -1571,9 +1571,9 @@ double table_us(int q, int N, int K, int batch, int terms) {
 
 // The kernel of a row-wise (terms = 0) or additive batch: the least estimated time,
 // a matrix-core kernel where it is 7% below the table kernel's (kernel 0: the
-// geometry of make_plan).  On 4576 drawn layers 0.7% of the calls are more than
-// 3% slower than the table kernel, 0.2% more than 10%, and the geometric mean
-// is 0.86 of its time (0.83 would be the best kernel for every layer).
+// geometry of make_plan).  On 4576 drawn layers 1% of the calls are more than 3%
+// slower than the table kernel, 0.4% more than 10%, and the geometric mean is 0.85
+// of its time (0.82 would be the best kernel for every layer).
 void make_matrix_plan(int q, int N, int K, int group, int terms, int batch, sa_matrix_plan* p) {
     *p = sa_matrix_plan{};
     if (batch < 2 || q > 4 || group % 128) return;
